@@ -147,7 +147,7 @@ int make_layout(const rogs_surfels* s, const rogs_camera* cams, int n_views,
   l.V = n_views;
   l.tw = tw;
   l.th = th;
-  l.ppl = tw * th / 64;
+  l.nw = tw * th / 64;
   l.stage = opts->stage ? opts->stage : 32;
   l.FS = feat_stride(l.C);
   l.GS = grad_stride(l.C);

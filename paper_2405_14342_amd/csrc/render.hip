@@ -1,16 +1,29 @@
 // Front-to-back alpha compositing of the sorted tile lists (Eq. 6) and its
 // adjoint.
 //
-// Mapping: one 64-lane wave per tile, tiles launched longest list first; a
-// tile of tile_w x tile_h = 64 * PPL pixels gives every lane PPL pixels of one
-// column, so the per-pair x offset is shared and each broadcast record read
-// from LDS feeds PPL pixels.  A wave starts from one precomputed record
-// (tile, list range, view) and reads each entry's slot directly, so the
-// prologue is two dependent global loads before the records arrive.
-// The wave stages KS list entries at a time in LDS (projection record +
-// the surfel's colour/semantic features), then every lane walks them in
-// order.  A pixel stops after the surfel that takes its transmittance below
-// t_eps; the wave leaves the list once all of its pixels have stopped.
+// Mapping: one 64-lane wave per 64 pixels (one pixel per lane), tiles launched
+// longest list first.  A tile of 64 pixels is one wave; a tile of 128 or 256
+// pixels is a block of 2 or 4 waves, each with a part of tile_w x (64 /
+// tile_w) pixels.  A wave starts from one precomputed record (tile, list
+// range, view) and reads each entry's slot directly, so the prologue is two
+// dependent global loads before the records arrive.  Entries are staged in
+// LDS (projection record + the surfel's colour/semantic features), then every
+// lane walks them in order.  A pixel stops after the surfel that takes its
+// transmittance below t_eps; the wave leaves the list once all of its pixels
+// have stopped.
+//
+// What bounds a large tile is the serial walk of its list: far from the
+// camera a 16 x 16 tile lists thousands of sub-pixel footprints, and the
+// launch ends with the longest list.  Splitting the tile's pixels over waves
+// (instead of 4 pixels per lane) makes an entry four times shorter, and the
+// test of each entry against the wave's own pixels (part_reached) leaves out
+// the half or more that reach other parts only.  Measured with 16 x 16 tiles,
+// 4 pixels per lane in one wave -> four waves with the test: 200k surfels x 6
+// views of 1600 x 900, C = 8: forward 563 -> 229 us, backward 666 -> 408 us,
+// fused step 918 -> 496 us; a 640 x 360 colour view of 3M surfels, C = 16:
+// forward 1029 -> 378 us.  One-wave tiles keep the untested walk in the fused
+// step and the backward: there at most 4 % of the entries a wave visits reach
+// none of its pixels, less than the test costs.
 //
 // Depth is composited relative to a reference depth t0 per pixel, the depth
 // of the first (nearest) list entry that reaches the pixel: D' = sum w (t_z -
@@ -54,18 +67,20 @@ __device__ __forceinline__ int find_view(const ViewDev* __restrict__ views, int 
 // List entries staged in LDS at a time: the template parameter KS of the
 // compositing kernels, 16, 32 or 64 (rogs_render_opts.stage).
 
-// Per-tile constants of the compositing kernels.
+// Per-wave constants of the compositing kernels: the tile and the 64 pixels of
+// it that this wave (part `part` of the tile) renders, one per lane.
 struct TileGeom {
-  int gt, v, W, H, px, py0, rows;
-  float pxc;
+  int gt, v, W, H, px, py, part;
+  float pxc, pyc;
+  float xa, xb, ya, yb;      // centres of the part's first and last pixel column and row
   uint32_t rbeg, rend, sbase;
   const ViewDev* vw;
 };
 
 __device__ __forceinline__ TileGeom tile_geom(const ViewDev* __restrict__ views, int N,
-                                              const uint4* __restrict__ tinfo) {
+                                              const uint4* __restrict__ tinfo, int part) {
   TileGeom t;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   // tile, list begin, list end, view | tile row << kViewBits
   const uint4 ti = tinfo[blockIdx.x];
   t.gt = (int)ti.x;
@@ -77,14 +92,57 @@ __device__ __forceinline__ TileGeom tile_geom(const ViewDev* __restrict__ views,
   const int ty = (int)(ti.w >> kViewBits), tx = lt - ty * t.vw->tiles_x;
   const int tw = t.vw->tw, th = t.vw->th;
   const int sh = __builtin_ctz((unsigned)tw);      // tile_w divides 64: a power of two
-  t.rows = 64 >> sh;
-  t.px = tx * tw + (lane & (tw - 1));
-  t.py0 = ty * th + (lane >> sh);
+  const int rows = 64 >> sh;
+  const int x0 = tx * tw, y0 = ty * th + part * rows;
+  t.part = part;
+  t.px = x0 + (lane & (tw - 1));
+  t.py = y0 + (lane >> sh);
   t.pxc = (float)t.px + 0.5f;
+  t.pyc = (float)t.py + 0.5f;
+  t.xa = (float)x0 + 0.5f;
+  t.xb = (float)(x0 + tw - 1) + 0.5f;
+  t.ya = (float)y0 + 0.5f;
+  t.yb = (float)(y0 + rows - 1) + 0.5f;
   t.rbeg = ti.y;
   t.rend = ti.z;
   t.sbase = (uint32_t)t.v * (uint32_t)N;
   return t;
+}
+
+// Whether an entry's footprint q <= q_cut can reach the pixel centres of a
+// part: false only if no pixel of the part passes the binary32 test, so
+// leaving the entry out changes no bit of the part.  The least value of the
+// quadratic form over the part's rectangle lies on the side facing the centre
+// in x or in y (or is 0 inside), with the other offset at its best value on
+// that side.  It is compared with the row spans' inflated cut, four times as
+// wide, q_cut (1 + 2^-16 / (1 - rho)): the binary32 rounding of the form,
+// here and in the pixel test, is below 2^-19 q / (1 - rho).  Entries whose
+// conic is too thin for that bound (1 - rho < 2^-12, axis ratio above ~90) or
+// out of its range are kept.
+__device__ __forceinline__ bool part_reached(const TileGeom& tg, const float4 r0, const float4 r1,
+                                             float qcut) {
+  const float A = r1.x, B2 = r1.y, C = r1.z;
+  const float lx = pixel_offset(tg.xa, r0.x, r0.z), hx = pixel_offset(tg.xb, r0.x, r0.z);
+  const float ly = pixel_offset(tg.ya, r0.y, r0.w), hy = pixel_offset(tg.yb, r0.y, r0.w);
+  const float dxn = fminf(fmaxf(lx, 0.0f), hx), dyn = fminf(fmaxf(ly, 0.0f), hy);
+  const float nb = -0.5f * B2;
+  const float dy1 = fminf(fmaxf(ly, nb * dxn * __builtin_amdgcn_rcpf(C)), hy);
+  const float dx2 = fminf(fmaxf(lx, nb * dyn * __builtin_amdgcn_rcpf(A)), hx);
+  const float q1 = pixel_q32(A, B2, C, dxn, dy1);
+  const float q2 = pixel_q32(A, B2, C, dx2, dyn);
+  const float ac = A * C;
+  const float gap = 1.0f - fabsf(nb) * __builtin_amdgcn_rsqf(ac);
+  const bool sure = gap >= 0x1p-12f && ac > 1e-24f && ac < 1e12f;
+  const float thr = qcut * (1.0f + 0x1p-16f * __builtin_amdgcn_rcpf(gap));
+  return !sure || !(q1 > thr && q2 > thr);
+}
+
+// Orders this wave's LDS writes before its later LDS reads (a wave-private
+// region: no barrier between waves).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Stages list entries [base, base + cnt) of the tile in LDS: the projection
@@ -114,105 +172,115 @@ __device__ __forceinline__ uint32_t stage_entries(uint32_t base, int cnt, uint32
   return e;
 }
 
-// Forward pass over the tile's list (Eq. 6): acc = sum w f (features, then
-// with kD the relative depth sum w (t_z - t0)), T, and nl = entries up to the
-// one that stopped the pixel.  With kD, t0 = the depth of the pixel's first
-// contributing entry: the list is in ascending depth, so the running minimum
-// of the contributing depths (FLT_MAX while none).  With kE, e_first = this
-// lane's emission index in the first staged batch.  ch (ROGS_CH_* bits,
+// The forward state of a pixel (Eq. 6): acc = sum w f (features, then with kD
+// the relative depth sum w (t_z - t0)), the transmittance T and nl = entries
+// up to the one that stopped the pixel.  With kD, t0 = the depth of the
+// pixel's first contributing entry: the list is in ascending depth, so the
+// running minimum of the contributing depths (FLT_MAX while none).
+template <int C>
+struct Pixel {
+  float acc[3 + C + 1];
+  float T, t0;
+  uint32_t nl;
+};
+
+template <int C>
+__device__ __forceinline__ void pixel_start(const TileGeom& tg, Pixel<C>& p) {
+  // a pixel is live while T >= t_eps (T only falls, and t_eps < 1); a pixel
+  // outside the image starts at T = 0, which no update changes
+  p.T = (tg.px < tg.W && tg.py < tg.H) ? 1.0f : 0.0f;
+  p.nl = 0;
+  p.t0 = FLT_MAX;
+#pragma unroll
+  for (int f = 0; f <= 3 + C; ++f) p.acc[f] = 0.0f;
+}
+
+// One staged list entry for a pixel; returns its footprint weight g.  seen =
+// the entry's position in the tile's list plus one.  ch (ROGS_CH_* bits,
 // uniform): the colour, semantic and depth sums are formed only when
-// selected; T, n_last and the order of operations do not depend on it.
+// selected; T, nl and the order of operations do not depend on it.
+// Lanes whose pixel the entry does not reach, or has stopped, run the same
+// arithmetic with g = 0: w = 0 leaves T and the sums as they are (T >= 0 and
+// every feature is finite), so the result is that of a branch around the
+// update without its exec-mask bookkeeping.
+template <int C, bool kD>
+__device__ __forceinline__ float entry_forward(const TileGeom& tg, const float4* s, uint32_t seen,
+                                               float qcut, float amax, float teps, uint32_t ch,
+                                               Pixel<C>& p) {
+  // every multiply-add is written out: the forward rounds the same in every
+  // kernel it is inlined into
+#pragma clang fp contract(off)
+  constexpr int F = 3 + C;            // composited features besides depth
+  constexpr int FS4 = (F + 4) / 4;    // float4 per feature record (features, alpha)
+  const float4 r0 = s[0], r1 = s[1];  // u_hi v_hi u_lo v_lo | A 2B C tz
+  float fv[FS4 * 4];
+#pragma unroll
+  for (int f = 0; f < FS4; ++f) {
+    const float4 t4 = s[2 + f];
+    fv[4 * f] = t4.x; fv[4 * f + 1] = t4.y; fv[4 * f + 2] = t4.z; fv[4 * f + 3] = t4.w;
+  }
+  const float al = fv[F];
+  const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
+  const float dy = pixel_offset(tg.pyc, r0.y, r0.w);
+  const float q = pixel_q32(r1.x, r1.y, r1.z, dx, dy);
+  const bool live = p.T >= teps;
+  const bool hit = live && q <= qcut;
+  // the exponential of every lane, then a select (no branch around it)
+  const float ge = gauss_weight(q);
+  const float g = hit ? ge : 0.0f;
+  const float a = clamp_alpha(al * g, amax);
+  const float w = a * p.T;
+  if (ch & ROGS_CH_RGB)
+#pragma unroll
+    for (int f = 0; f < 3; ++f) p.acc[f] = __builtin_fmaf(w, fv[f], p.acc[f]);
+  if (ch & ROGS_CH_SEM)
+#pragma unroll
+    for (int f = 3; f < F; ++f) p.acc[f] = __builtin_fmaf(w, fv[f], p.acc[f]);
+  if (kD && (ch & ROGS_CH_D)) {
+    p.t0 = hit ? fminf(p.t0, r1.w) : p.t0;
+    p.acc[F] = __builtin_fmaf(w, r1.w - p.t0, p.acc[F]);
+  }
+  p.T -= w;                     // T (1 - alpha)
+  // at the entry that stops the pixel, its position in the list plus one
+  p.nl = live ? seen : p.nl;
+  return g;
+}
+
+// Whether every pixel of the wave has stopped (every lane runs this together).
+template <int C>
+__device__ __forceinline__ bool all_stopped(const Pixel<C>& p, float teps) {
+  return __builtin_amdgcn_ballot_w64(p.T >= teps) == 0;
+}
+
 constexpr int kFwdUnroll = 4;       // forward entries per stop test
 
-// With kG (16, one pixel per lane) the footprint weights g of the list's
-// first kG entries are kept in gsave for the backward: gsave[j] is the
-// weight of every entry the forward evaluates, which covers each pixel's
-// entries before n_last, the only ones the backward reads it for, and 0 for
-// the others (past the list's end or after the whole wave has stopped).
-template <int C, int PPL, int KS, bool kE, bool kD, int kG = 0>
+// Forward pass of a one-wave tile (64 pixels) over its list, KS staged entries
+// at a time.  e_first = this lane's emission index in the first staged batch.
+// With kG (16) the footprint weights g of the list's first kG entries are kept
+// in gsave for the backward: gsave[j] is the weight of every entry the forward
+// evaluates, which covers each pixel's entries before n_last, the only ones
+// the backward reads it for, and 0 for the others (past the list's end or
+// after the whole wave has stopped).
+template <int C, int KS, int kG>
 __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, float amax,
                                              float teps, const uint32_t* __restrict__ vals,
                                              const uint32_t* __restrict__ spair,
                                              const float4* __restrict__ rec,
-                                             const float4* __restrict__ feat, float4* s_r0,
-                                             float4* s_r1, float4* s_f, const float* pyc,
-                                             float (*acc)[3 + C + 1], float* T, uint32_t* nl,
-                                             uint32_t& e_first, float* t0, uint32_t ch,
-                                             float* gsave = nullptr) {
-  // every multiply-add is written out: the forward rounds the same in every
-  // kernel it is inlined into
-#pragma clang fp contract(off)
-  static_assert(kG == 0 || (kG == 16 && PPL == 1 && KS >= kG), "kept weights");
-  constexpr int F = 3 + C;            // composited features besides depth
-  constexpr int FS4 = (F + 4) / 4;    // float4 per feature record (features, alpha)
-  // a pixel is live while T >= t_eps (T only falls, and t_eps < 1); a pixel
-  // outside the image starts at T = 0, which no update changes
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int py = tg.py0 + k * tg.rows;
-    T[k] = (tg.px < tg.W && py < tg.H) ? 1.0f : 0.0f;
-    nl[k] = 0;
-    if (kD) t0[k] = FLT_MAX;
-#pragma unroll
-    for (int f = 0; f <= F; ++f) acc[k][f] = 0.0f;
-  }
+                                             const float4* __restrict__ feat, float4* s_st,
+                                             Pixel<C>& p, uint32_t& e_first, uint32_t ch,
+                                             float* gsave) {
+  static_assert(kG == 0 || (kG == 16 && KS >= kG), "kept weights");
+  constexpr int FS4 = (3 + C + 4) / 4;
+  constexpr int ES = 2 + FS4;
+  pixel_start<C>(tg, p);
   bool stop_all = false;
   for (uint32_t base = tg.rbeg; base < tg.rend && !stop_all; base += KS) {
     const int cnt = (int)min((uint32_t)KS, tg.rend - base);
-    const uint32_t e =
-        stage_entries<FS4, kE>(base, cnt, tg.sbase, vals, spair, rec, feat, s_r0, s_r1, s_f);
+    const uint32_t seen0 = base - tg.rbeg + 1u;
+    const uint32_t e = stage_entries<FS4, true>(base, cnt, tg.sbase, vals, spair, rec, feat, s_st,
+                                                s_st + 1, s_st + 2);
     if (base == tg.rbeg) e_first = e;
     __syncthreads();
-    // one list entry for every pixel of the lane (gout: its g, or nullptr)
-    auto fentry = [&](const int j, float* gout) {
-      const float4 r0 = s_r0[j * (2 + FS4)], r1 = s_r1[j * (2 + FS4)];   // u_hi v_hi u_lo v_lo | A 2B C tz
-      float fv[FS4 * 4];
-#pragma unroll
-      for (int f = 0; f < FS4; ++f) {
-        const float4 t4 = s_f[j * (2 + FS4) + f];
-        fv[4 * f] = t4.x; fv[4 * f + 1] = t4.y; fv[4 * f + 2] = t4.z; fv[4 * f + 3] = t4.w;
-      }
-      const float al = fv[F];
-      const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
-      // Lanes whose pixel the entry does not reach, or has stopped, run the
-      // same arithmetic with g = 0: w = 0 leaves T and the sums as they are
-      // (T >= 0 and every feature is finite), so the result is that of a
-      // branch around the update without its exec-mask bookkeeping.
-#pragma unroll
-      for (int k = 0; k < PPL; ++k) {
-        const float dy = pixel_offset(pyc[k], r0.y, r0.w);
-        const float q = pixel_q32(r1.x, r1.y, r1.z, dx, dy);
-        const bool live = T[k] >= teps;
-        const bool hit = live && q <= qcut;
-        // the exponential of every lane, then a select (no branch around it)
-        const float ge = gauss_weight(q);
-        const float g = hit ? ge : 0.0f;
-        if (gout) gout[k] = g;
-        const float a = clamp_alpha(al * g, amax);
-        const float w = a * T[k];
-        if (ch & ROGS_CH_RGB)
-#pragma unroll
-          for (int f = 0; f < 3; ++f) acc[k][f] = __builtin_fmaf(w, fv[f], acc[k][f]);
-        if (ch & ROGS_CH_SEM)
-#pragma unroll
-          for (int f = 3; f < F; ++f) acc[k][f] = __builtin_fmaf(w, fv[f], acc[k][f]);
-        if (kD && (ch & ROGS_CH_D)) {
-          t0[k] = hit ? fminf(t0[k], r1.w) : t0[k];
-          acc[k][F] = __builtin_fmaf(w, r1.w - t0[k], acc[k][F]);
-        }
-        T[k] -= w;                     // T (1 - alpha)
-        // entries seen while live: at the entry that stops the pixel, its
-        // position in the list plus one
-        nl[k] += live ? 1u : 0u;
-      }
-    };
-    // every lane of the wave runs this loop: the ballot is the stop test
-    auto all_stopped = [&]() {
-      bool live = false;
-#pragma unroll
-      for (int k = 0; k < PPL; ++k) live = live || T[k] >= teps;
-      return __builtin_amdgcn_ballot_w64(live) == 0;
-    };
     // groups of kFwdUnroll entries, the stop test after each group: entries
     // past a pixel's stop change nothing for it, so the results are those
     // of a test after every entry.  The first kG entries of the list are
@@ -223,8 +291,8 @@ __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, flo
 #pragma unroll
       for (int j = 0; j < kG; ++j) {
         if (j < cnt && !stop_all) {
-          fentry(j, gsave + j);
-          if (j % kFwdUnroll == kFwdUnroll - 1 && all_stopped()) stop_all = true;
+          gsave[j] = entry_forward<C, false>(tg, s_st + j * ES, seen0 + j, qcut, amax, teps, ch, p);
+          if (j % kFwdUnroll == kFwdUnroll - 1 && all_stopped<C>(p, teps)) stop_all = true;
         } else {
           gsave[j] = 0.0f;
         }
@@ -236,53 +304,114 @@ __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, flo
       for (int u = 0; u < kFwdUnroll; ++u) {
         const int j = j0 + u;
         if (j >= cnt) break;
-        fentry(j, nullptr);
+        (void)entry_forward<C, false>(tg, s_st + j * ES, seen0 + j, qcut, amax, teps, ch, p);
       }
-      if (all_stopped()) stop_all = true;
+      if (all_stopped<C>(p, teps)) stop_all = true;
     }
     __syncthreads();
   }
 }
 
-typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-
-// Floats of the backward's LDS block for one block of 16 list entries: the
-// per-pixel weights w of 16 entries (rows of 64 * PPL + 4 floats), also used
-// once per tile to transpose the per-pixel gradient vectors.
-template <int C, int PPL>
-__host__ __device__ constexpr int bwd_lds_floats() {
-  constexpr int NFB = (3 + C + 1 + 15) / 16;
-  constexpr int a = 16 * (64 * PPL + 4), b = 64 * PPL * (16 * NFB + 1);
-  return a > b ? a : b;
+// Forward pass of one part (wave) of a tile over the tile's list, 64 entries
+// at a time: every lane tests one entry against the part (part_reached) and
+// the entries that reach it are staged side by side in the wave's own LDS
+// region, so the waves of a tile share no barrier and each walks only the
+// entries that its own 64 pixels can see.  The records of the next 64 entries
+// are requested before the present ones are walked.
+template <int C, bool kD>
+__device__ __forceinline__ void forward_part(const TileGeom& tg, float qcut, float amax,
+                                             float teps, const uint32_t* __restrict__ spair,
+                                             const float4* __restrict__ rec,
+                                             const float4* __restrict__ feat, float4* s_st,
+                                             Pixel<C>& p, uint32_t ch) {
+  constexpr int FS4 = (3 + C + 4) / 4;
+  constexpr int ES = 2 + FS4;
+  const int lane = threadIdx.x & 63;
+  pixel_start<C>(tg, p);
+  if (all_stopped<C>(p, teps)) return;      // a part outside the image
+  const uint32_t len = tg.rend - tg.rbeg;
+  uint32_t slot = 0, slot1 = 0;
+  float4 r0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), r1 = r0;
+  if ((uint32_t)lane < len) {
+    slot = spair[tg.rbeg + lane];
+    r0 = rec[2 * (size_t)slot];
+    r1 = rec[2 * (size_t)slot + 1];
+  }
+  if ((uint32_t)lane + 64u < len) slot1 = spair[tg.rbeg + 64u + lane];
+  for (uint32_t base = 0; base < len; base += 64u) {
+    r1.y *= 2.0f;                                        // A, 2B, C, t_z
+    const bool in = base + lane < len && part_reached(tg, r0, r1, qcut);
+    unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+    const int n = (int)__popcll(m);
+    if (in) {
+      const int j = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      float4* s = s_st + j * ES;
+      const float4* fr = feat + (size_t)(slot - tg.sbase) * FS4;
+      s[0] = r0;
+      s[1] = r1;
+#pragma unroll
+      for (int f = 0; f < FS4; ++f) s[2 + f] = fr[f];
+    }
+    slot = slot1;
+    if (base + 64u + lane < len) {
+      r0 = rec[2 * (size_t)slot];
+      r1 = rec[2 * (size_t)slot + 1];
+    }
+    if (base + 128u + lane < len) slot1 = spair[tg.rbeg + base + 128u + lane];
+    wave_lds_sync();
+    bool stop = false;
+    for (int j0 = 0; j0 < n && !stop; j0 += kFwdUnroll) {
+#pragma unroll
+      for (int u = 0; u < kFwdUnroll; ++u) {
+        const int j = j0 + u;
+        if (j >= n) break;
+        const uint32_t seen = base + (uint32_t)__builtin_ctzll(m) + 1u;
+        m &= m - 1ull;
+        (void)entry_forward<C, kD>(tg, s_st + j * ES, seen, qcut, amax, teps, ch, p);
+      }
+      stop = all_stopped<C>(p, teps);
+    }
+    wave_lds_sync();
+    if (stop) break;
+  }
 }
 
+typedef float mfma_f4 __attribute__((ext_vector_type(4)));
+
+// Floats of a wave's LDS block for one block of 16 list entries: the
+// per-pixel weights w of 16 entries (rows of 64 + 4 floats), also used once
+// per tile to transpose the per-pixel gradient vectors, 16 columns at a time
+// (rows of 16 + 1 floats).
+constexpr int kWRow = 64 + 4;
+constexpr int kWFloats = 16 * kWRow;
+static_assert(kWFloats >= 64 * 17, "transpose space");
+
+// Column blocks of 16 of the feature and depth gradients.
+template <int C>
+constexpr int kNFB() { return (3 + C + 1 + 15) / 16; }
+
 // Feature and depth gradients of up to 16 list entries as one matrix product
-// on the matrix cores: D[m][n] = sum over the tile's pixels p of
+// on the matrix cores: D[m][n] = sum over the wave's pixels p of
 // w[m][p] * gamma[p][n], where gamma[p] = (dL/dfeatures, dL/dD) of pixel p.
 // v_mfma_f32_16x16x4_f32 takes A[m][k] from lane m + 16k, B[k][n] from lane
 // n + 16k and returns D[4g + i][n] in lane n + 16g, element i.  The k-th
-// step of 4 covers pixels kk * 64 + kgrp * 16 + c, so a lane reads its A
-// operands as 16 contiguous floats of its entry's row.
-template <int C, int PPL>
+// step of 4 covers pixels kgrp * 16 + c, so a lane reads its A operands as 16
+// contiguous floats of its entry's row.  Row m goes to record s_e[m] of dst.
+template <int C>
 __device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s_e, int nrows,
-                                             const float (&bG)[(3 + C + 1 + 15) / 16][PPL][16],
-                                             float* __restrict__ gpair) {
+                                             const float (&bG)[kNFB<C>()][16], float* dst) {
   constexpr int F = 3 + C;
   constexpr uint32_t GS = grad_stride_c(C);
   constexpr int NG = F + 1;
-  constexpr int NFB = (NG + 15) / 16;
-  constexpr int WS = 64 * PPL + 4;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   const int mrow = lane & 15, kgrp = lane >> 4;
-  float a[PPL][16];
+  float a[16];
+  const float4* ap = reinterpret_cast<const float4*>(s_w + mrow * kWRow + kgrp * 16);
 #pragma unroll
-  for (int kk = 0; kk < PPL; ++kk) {
-    const float4* ap = reinterpret_cast<const float4*>(s_w + mrow * WS + kk * 64 + kgrp * 16);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = ap[q];
-      a[kk][4 * q] = t.x; a[kk][4 * q + 1] = t.y; a[kk][4 * q + 2] = t.z; a[kk][4 * q + 3] = t.w;
-    }
+  for (int q = 0; q < 4; ++q) {
+    const float4 t = ap[q];
+    a[4 * q] = t.x; a[4 * q + 1] = t.y; a[4 * q + 2] = t.z; a[4 * q + 3] = t.w;
   }
   uint32_t e4[4];
   bool ok[4];
@@ -293,98 +422,162 @@ __device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s
     e4[i] = s_e[m];
   }
 #pragma unroll
-  for (int nb = 0; nb < NFB; ++nb) {
+  for (int nb = 0; nb < kNFB<C>(); ++nb) {
     mfma_f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int kk = 0; kk < PPL; ++kk)
-#pragma unroll
-      for (int c = 0; c < 16; ++c)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][c], bG[nb][kk][c], acc, 0, 0, 0);
+    for (int c = 0; c < 16; ++c)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], bG[nb][c], acc, 0, 0, 0);
     const int n = nb * 16 + mrow;
     if (n < NG) {
       const int col = n < F ? 7 + n : 6;       // record: ..., dt_z (6), features (7 ...)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (ok[i]) gpair[(size_t)e4[i] * GS + col] = acc[i];
+        if (ok[i]) dst[(size_t)e4[i] * GS + col] = acc[i];
     }
   }
 }
 
-// Backward pass over the tile's list, given per pixel the output gradient
-// Gv (features, depth, alpha), G.O (with the relative depth D'), T_final,
-// n_last and the reference depth t0 (used with kDA).  Writes one record of NV
-// gradient values per pair at its emission index: the five moments and
-// dalpha are summed across the wave with a reduce-scatter, the feature and
-// depth gradients come from feature_gemm once per 16 entries.  With kG (16,
-// one pixel per lane) gsave holds the forward's footprint weights of the
-// list's first kG entries, valid for the entries before n_last.
-template <int C, int PPL, int KS, bool kDA, int kG = 0>
+// A pixel's inputs of the backward: the output gradient Gv (features, depth,
+// alpha), G.O (with the relative depth D'), T_final, n_last and the reference
+// depth t0 (used with kDA).
+template <int C>
+struct PixelGrad {
+  float Gv[3 + C + 2];
+  float GO, Tf, t0;
+  uint32_t nl;
+};
+
+// The backward's running state of a pixel: the transmittance and the prefix
+// sum of w gf over the entries so far, and the alpha channel's gradient term.
+struct PixelBack {
+  float T, Spre, GAf;
+};
+
+template <int C, bool kDA>
+__device__ __forceinline__ PixelBack back_start(const PixelGrad<C>& pg) {
+#pragma clang fp contract(off)
+  constexpr int F = 3 + C;
+  PixelBack b;
+  b.T = 1.0f;
+  b.Spre = 0.0f;
+  // D = D' + t0 A: the alpha channel's gradient carries t0 dL/dD, times
+  // T_final for dA/d(alpha_k) = T_final / (1 - alpha_k)
+  b.GAf = kDA ? __builtin_fmaf(pg.t0, pg.Gv[F], pg.Gv[F + 1]) * pg.Tf : 0.0f;
+  return b;
+}
+
+// B operand of feature_gemm: gamma[pixel][n] for pixel kgrp * 16 + c,
+// transposed through the wave's LDS block.
+template <int C>
+__device__ __forceinline__ void transpose_grad(const PixelGrad<C>& pg, float* s_w,
+                                               float (&bG)[kNFB<C>()][16]) {
+  constexpr int F = 3 + C;
+  const int lane = threadIdx.x & 63;
+  const int mrow = lane & 15, kgrp = lane >> 4;
+#pragma unroll
+  for (int nb = 0; nb < kNFB<C>(); ++nb) {
+    float* row = s_w + lane * 17;
+#pragma unroll
+    for (int n = 0; n < 16; ++n) row[n] = 16 * nb + n <= F ? pg.Gv[16 * nb + n] : 0.0f;
+    wave_lds_sync();
+#pragma unroll
+    for (int c = 0; c < 16; ++c) bG[nb][c] = s_w[(kgrp * 16 + c) * 17 + mrow];
+    wave_lds_sync();
+  }
+}
+
+constexpr int kReduced = 6;     // gradient values per entry summed across the wave
+
+// One staged list entry of the backward for a pixel with footprint weight g
+// (0 where the entry does not reach it): its weight w and pv = the five
+// moments of gda and dalpha.
+//   per pair: sum gda dx, sum gda dy, sum gda dx^2, sum gda dx dy,
+//   sum gda dy^2 (gda = dL/d(alpha) per pixel; dL/dq = -(alpha / 2) gda),
+//   dalpha = sum gda, dtz, drgb[3], dsem[C]
+// Lanes whose pixel the pair does not reach run the same arithmetic with
+// g = 0: alpha = w = 0, T and the prefix unchanged, terms +-0 (a pair that
+// reaches no pixel of the wave gets a zero record this way; a branch around
+// it would copy T and the prefix on every entry).
+template <int C, bool kDA>
+__device__ __forceinline__ float entry_backward(const float* fv, float tz, float dx, float dy,
+                                                float g, float amax, const PixelGrad<C>& pg,
+                                                PixelBack& b, float (&pv)[kReduced]) {
+  // every multiply-add is written out: the backward rounds the same in the
+  // fused step and in the stand-alone backward
+#pragma clang fp contract(off)
+  constexpr int F = 3 + C;
+  const float araw = fv[F] * g;
+  const float a = clamp_alpha(araw, amax);
+  const float w = a * b.T;
+  float gf = kDA ? pg.Gv[F] * (tz - pg.t0) : 0.0f;
+#pragma unroll
+  for (int f = 0; f < F; ++f) gf = __builtin_fmaf(pg.Gv[f], fv[f], gf);
+  const float om = 1.0f - a;
+  const float inv = __builtin_amdgcn_rcpf(om);
+  // the suffix G.O - sum over entries up to this one of w gf
+  b.Spre = __builtin_fmaf(w, gf, b.Spre);
+  const float suffix = pg.GO - b.Spre;
+  float da = __builtin_fmaf(b.T, gf, -(suffix * inv));
+  if (kDA) da = __builtin_fmaf(b.GAf, inv, da);
+  // the clamp cuts alpha's dependence on g: gda = g da is dL/d(alpha)
+  // where it does not hold (0 where it does), and dL/dq = -(alpha / 2)
+  // gda, the factor -alpha / 2 being applied to the slot's sums by
+  // the projection adjoint
+  const float gda = araw > amax ? 0.0f : g * da;
+  // moments of gda over the pixel offsets; the projection adjoint
+  // turns them into dL/d(u, v, A, B, C) with the pair's conic
+  const float gx = gda * dx, gy = gda * dy;
+  pv[5] = gda;
+  pv[0] = gx;
+  pv[1] = gy;
+  pv[2] = gx * dx;
+  pv[3] = gx * dy;
+  pv[4] = gy * dy;
+  b.T -= w;                       // as in the forward
+  return w;
+}
+
+template <int FS4>
+__device__ __forceinline__ void load_features(const float4* s, float* fv) {
+#pragma unroll
+  for (int f = 0; f < FS4; ++f) {
+    const float4 t4 = s[2 + f];
+    fv[4 * f] = t4.x; fv[4 * f + 1] = t4.y; fv[4 * f + 2] = t4.z; fv[4 * f + 3] = t4.w;
+  }
+}
+
+// Backward pass of a one-wave tile (64 pixels) over its list.  Writes one
+// record of NV gradient values per pair at its emission index: the five
+// moments and dalpha are summed across the wave with a reduce-scatter, the
+// feature and depth gradients come from feature_gemm once per 16 entries.
+// With kG (16) gsave holds the forward's footprint weights of the list's
+// first kG entries, valid for the entries before n_last.
+template <int C, int KS, bool kDA, int kG>
 __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, float amax,
                                               const uint32_t* __restrict__ vals,
                                               const uint32_t* __restrict__ spair,
                                               const float4* __restrict__ rec,
-                                              const float4* __restrict__ feat, float4* s_r0,
-                                              float4* s_r1, float4* s_f, float* s_w,
-                                              uint32_t* s_e, const float* pyc,
-                                              const float (*Gv)[3 + C + 2], const float* GO,
-                                              const float* Tf, const uint32_t* nl,
+                                              const float4* __restrict__ feat, float4* s_st,
+                                              float* s_w, uint32_t* s_e, const PixelGrad<C>& pg,
                                               float* __restrict__ gpair, bool staged,
-                                              uint32_t e_pre, const float* t0,
-                                              const float* gsave = nullptr) {
-  // every multiply-add is written out: the backward rounds the same in the
-  // fused step and in the stand-alone backward
-#pragma clang fp contract(off)
-  static_assert(kG == 0 || (kG == 16 && PPL == 1 && KS >= kG), "kept weights");
+                                              uint32_t e_pre, const float* gsave) {
+  static_assert(kG == 0 || (kG == 16 && KS >= kG), "kept weights");
   constexpr int F = 3 + C;
   constexpr int FS4 = (F + 4) / 4;
-  // per pair: sum gda dx, sum gda dy, sum gda dx^2, sum gda dx dy,
-  // sum gda dy^2 (gda = dL/d(alpha) per pixel; dL/dq = -(alpha / 2) gda),
-  // dalpha = sum gda, dtz, drgb[3], dsem[C]
+  constexpr int ES = 2 + FS4;
   constexpr int NV = 10 + C;
   constexpr uint32_t GS = grad_stride_c(C);   // floats per record
-  constexpr int NR = 6;                       // reduced across the wave
-  constexpr int NFB = (F + 1 + 15) / 16;
-  constexpr int WS = 64 * PPL + 4;
+  constexpr int NR = kReduced;
   const int lane = threadIdx.x;
   const int my_comp = rs_comp(lane, NR);
   const bool writer = my_comp >= 0 && (lane & rs_dup_bits(NR)) == 0;
-  float T[PPL], Spre[PPL], GAf[PPL];
-  uint32_t maxn = 0;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    T[k] = 1.0f;
-    Spre[k] = 0.0f;
-    maxn = max(maxn, nl[k]);
-    // D = D' + t0 A: the alpha channel's gradient carries t0 dL/dD, times
-    // T_final for dA/d(alpha_k) = T_final / (1 - alpha_k)
-    GAf[k] = kDA ? __builtin_fmaf(t0[k], Gv[k][F], Gv[k][F + 1]) * Tf[k] : 0.0f;
-  }
+  PixelBack b = back_start<C, kDA>(pg);
   // every lane holds the maximum: as a scalar the list loop is scalar control
-  maxn = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(maxn));
+  const uint32_t maxn = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(pg.nl));
   const uint32_t stop = tg.rbeg + min(maxn, tg.rend - tg.rbeg);
-  // B operand of feature_gemm: gamma[pixel][n] for pixel kk * 64 + kgrp * 16
-  // + c, transposed through LDS (pixel-major rows of 16 * NFB + 1 floats);
   // not needed when no entry is visited
-  float bG[NFB][PPL][16];
-  if (stop > tg.rbeg) {
-    constexpr int GR = 16 * NFB + 1;
-    const int mrow = lane & 15, kgrp = lane >> 4;
-#pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-      float* row = s_w + (k * 64 + lane) * GR;
-#pragma unroll
-      for (int n = 0; n < 16 * NFB; ++n) row[n] = n <= F ? Gv[k][n] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int nb = 0; nb < NFB; ++nb)
-#pragma unroll
-      for (int kk = 0; kk < PPL; ++kk)
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-          bG[nb][kk][c] = s_w[(kk * 64 + kgrp * 16 + c) * GR + nb * 16 + mrow];
-    __syncthreads();
-  }
+  float bG[kNFB<C>()][16];
+  if (stop > tg.rbeg) transpose_grad<C>(pg, s_w, bG);
   // this lane's column of the reduced values in every record: lanes that
   // hold a copy of a component write the same bits to the same address, and
   // where the record has padding, the lanes without a component write
@@ -396,8 +589,8 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
     // a list the forward staged whole is still in LDS
     const uint32_t e_mine =
         staged ? e_pre
-               : stage_entries<FS4, true>(base, cnt, tg.sbase, vals, spair, rec, feat, s_r0,
-                                          s_r1, s_f);
+               : stage_entries<FS4, true>(base, cnt, tg.sbase, vals, spair, rec, feat, s_st,
+                                          s_st + 1, s_st + 2);
     if (lane < KS) s_e[lane] = e_mine;
     __syncthreads();
     // blocks of 16 entries: the per-entry pass, then their feature gradients
@@ -405,82 +598,28 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
       const int j1 = min(j0 + 16, cnt);
       // two entries per iteration (immediate LDS offsets, half the loop
       // bookkeeping); the second is skipped past the block's end
-      // gk: the pixels' kept weights of entry j, or nullptr
+      // gk: the pixel's kept weight of entry j, or nullptr
       auto entry = [&](const int j, const float* gk) {
+#pragma clang fp contract(off)
         const uint32_t idx = base - tg.rbeg + (uint32_t)j;
         const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)e_mine, j);
-        const float4 r0 = s_r0[j * (2 + FS4)], r1 = s_r1[j * (2 + FS4)];
-        const float A = r1.x, B2 = r1.y, Cc = r1.z, tz = r1.w;
+        const float4* s = s_st + j * ES;
+        const float4 r0 = s[0], r1 = s[1];
         const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
-        float* wrow = s_w + (j - j0) * WS + lane;
-        float dy[PPL], gw[PPL];
-#pragma unroll
-        for (int k = 0; k < PPL; ++k) {
-          dy[k] = pixel_offset(pyc[k], r0.y, r0.w);
-          if (gk) {
-            gw[k] = idx < nl[k] ? gk[k] : 0.0f;
-          } else {
-            const float q = pixel_q32(A, B2, Cc, dx, dy[k]);
-            const float ge = gauss_weight(q);
-            gw[k] = (idx < nl[k] && q <= qcut) ? ge : 0.0f;
-          }
+        const float dy = pixel_offset(tg.pyc, r0.y, r0.w);
+        float g;
+        if (gk) {
+          g = idx < pg.nl ? *gk : 0.0f;
+        } else {
+          const float q = pixel_q32(r1.x, r1.y, r1.z, dx, dy);
+          const float ge = gauss_weight(q);
+          g = (idx < pg.nl && q <= qcut) ? ge : 0.0f;
         }
         float fv[FS4 * 4];
-#pragma unroll
-        for (int f = 0; f < FS4; ++f) {
-          const float4 t4 = s_f[j * (2 + FS4) + f];
-          fv[4 * f] = t4.x; fv[4 * f + 1] = t4.y; fv[4 * f + 2] = t4.z; fv[4 * f + 3] = t4.w;
-        }
-        const float al = fv[F];
-        // Lanes whose pixel the pair does not reach run the same arithmetic
-        // with g = 0: alpha = w = 0, T and the prefix unchanged, terms +-0 (a
-        // pair that reaches no pixel of the tile gets a zero record this way;
-        // a branch around it would copy T and the prefix on every entry).
+        load_features<FS4>(s, fv);
         float pv[NR];
-#pragma unroll
-        for (int k = 0; k < PPL; ++k) {
-          const float g = gw[k];
-          const float araw = al * g;
-          const float a = clamp_alpha(araw, amax);
-          const float w = a * T[k];
-          wrow[k * 64] = w;
-          float gf = kDA ? Gv[k][F] * (tz - t0[k]) : 0.0f;
-#pragma unroll
-          for (int f = 0; f < F; ++f) gf = __builtin_fmaf(Gv[k][f], fv[f], gf);
-          const float om = 1.0f - a;
-          const float inv = __builtin_amdgcn_rcpf(om);
-          // the suffix G.O - sum over entries up to this one of w gf
-          Spre[k] = __builtin_fmaf(w, gf, Spre[k]);
-          const float suffix = GO[k] - Spre[k];
-          float da = __builtin_fmaf(T[k], gf, -(suffix * inv));
-          if (kDA) da = __builtin_fmaf(GAf[k], inv, da);
-          // the clamp cuts alpha's dependence on g: gda = g da is dL/d(alpha)
-          // where it does not hold (0 where it does), and dL/dq = -(alpha / 2)
-          // gda, the factor -alpha / 2 being applied to the slot's sums by
-          // the projection adjoint
-          const float gda = araw > amax ? 0.0f : g * da;
-          // moments of gda over the pixel offsets; the projection adjoint
-          // turns them into dL/d(u, v, A, B, C) with the pair's conic (the
-          // first pixel of a lane sets the values, later ones add to them)
-          const float dyk = dy[k];
-          const float gx = gda * dx, gy = gda * dyk;
-          if (k == 0) {
-            pv[5] = gda;
-            pv[0] = gx;
-            pv[1] = gy;
-            pv[2] = gx * dx;
-            pv[3] = gx * dyk;
-            pv[4] = gy * dyk;
-          } else {
-            pv[5] += gda;
-            pv[0] += gx;
-            pv[1] += gy;
-            pv[2] = __builtin_fmaf(gx, dx, pv[2]);
-            pv[3] = __builtin_fmaf(gx, dyk, pv[3]);
-            pv[4] = __builtin_fmaf(gy, dyk, pv[4]);
-          }
-          T[k] -= w;                       // as in the forward
-        }
+        s_w[(j - j0) * kWRow + lane] =
+            entry_backward<C, kDA>(fv, r1.w, dx, dy, g, amax, pg, b, pv);
         const float tot = wave_reduce_scatter<NR>(pv, lane);
         if (kPadCol || writer) gcol[(size_t)e * GS] = tot;
       };
@@ -497,7 +636,7 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
         }
       }
       __syncthreads();
-      feature_gemm<C, PPL>(s_w, s_e + j0, j1 - j0, bG, gpair);
+      feature_gemm<C>(s_w, s_e + j0, j1 - j0, bG, gpair);
       __syncthreads();
     }
     __syncthreads();
@@ -509,15 +648,134 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
   }
 }
 
+// LDS of a tile of NW waves (parts) in the backward: the staged entries, the
+// waves' weight rows and partial records, and per wave which staged entries it
+// took part in and the rows of its present block of 16.
+template <int C, int NW, int KS>
+struct alignas(16) BlockLds {
+  float4 st[KS * (2 + (3 + C + 4) / 4)];
+  float w[NW][kWFloats];
+  float part[NW][NW == 1 ? 4 : KS * grad_stride_c(C)];    // one wave writes its records directly
+  unsigned long long mask[NW];
+  uint32_t row[NW][16];
+  uint32_t e[KS];
+  uint32_t maxn[NW];
+};
+
+// Backward pass of a tile of NW waves.  The block stages KS list entries; each
+// wave tests them against its own part (lane j tests entry j), walks the ones
+// that reach it in blocks of 16 and leaves its partial record of each in LDS;
+// then the block adds the waves' partials in wave order and writes each pair's
+// record whole.  A wave whose part an entry does not reach adds nothing.
+template <int C, int NW, int KS, bool kDA>
+__device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, float amax,
+                                               const uint32_t* __restrict__ vals,
+                                               const uint32_t* __restrict__ spair,
+                                               const float4* __restrict__ rec,
+                                               const float4* __restrict__ feat,
+                                               BlockLds<C, NW, KS>& L, const PixelGrad<C>& pg,
+                                               float* __restrict__ gpair) {
+  constexpr int F = 3 + C;
+  constexpr int FS4 = (F + 4) / 4;
+  constexpr int ES = 2 + FS4;
+  constexpr int NV = 10 + C;
+  constexpr uint32_t GS = grad_stride_c(C);
+  constexpr int Q = (int)GS / 4;
+  constexpr int NR = kReduced;
+  constexpr int NT = 64 * NW;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* const s_w = L.w[wv];
+  float* const s_p = L.part[wv];
+  const int my_comp = rs_comp(lane, NR);
+  constexpr bool kPadCol = GS > (uint32_t)NV;
+  const bool writer = kPadCol || (my_comp >= 0 && (lane & rs_dup_bits(NR)) == 0);
+  float* const pcol = s_p + (my_comp >= 0 ? my_comp : (kPadCol ? NV : 0));
+  PixelBack b = back_start<C, kDA>(pg);
+  const uint32_t my_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(pg.nl));
+  if (lane == 0) L.maxn[wv] = my_max;
+  __syncthreads();
+  uint32_t maxn = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) maxn = max(maxn, L.maxn[w]);
+  const uint32_t stop = tg.rbeg + min(maxn, tg.rend - tg.rbeg);
+  float bG[kNFB<C>()][16];
+  if (my_max > 0u) transpose_grad<C>(pg, s_w, bG);
+  for (uint32_t base = tg.rbeg; base < stop; base += KS) {
+    const int cnt = (int)min((uint32_t)KS, stop - base);
+    if (tid < cnt) L.e[tid] = vals[base + tid];
+    for (int t = tid; t < cnt * ES; t += NT) {
+      const int j = t / ES, c = t - j * ES;
+      const uint32_t slot = spair[base + j];
+      float4 x = c < 2 ? rec[2 * (size_t)slot + c]
+                       : feat[(size_t)(slot - tg.sbase) * FS4 + (c - 2)];
+      if (c == 1) x.y *= 2.0f;                            // A, 2B, C, t_z
+      L.st[t] = x;
+    }
+    __syncthreads();
+    const uint32_t seen = base - tg.rbeg;
+    const bool in = lane < cnt && seen + (uint32_t)lane < my_max &&
+                    part_reached(tg, L.st[min(lane, KS - 1) * ES], L.st[min(lane, KS - 1) * ES + 1],
+                                 qcut);
+    unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+    if (lane == 0) L.mask[wv] = m;
+    while (m) {
+      int n = 0;
+      for (; n < 16 && m; ++n) {
+#pragma clang fp contract(off)
+        const int j = __builtin_ctzll(m);
+        m &= m - 1ull;
+        const float4* s = L.st + j * ES;
+        const float4 r0 = s[0], r1 = s[1];
+        const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
+        const float dy = pixel_offset(tg.pyc, r0.y, r0.w);
+        const float q = pixel_q32(r1.x, r1.y, r1.z, dx, dy);
+        const float ge = gauss_weight(q);
+        const float g = (seen + (uint32_t)j < pg.nl && q <= qcut) ? ge : 0.0f;
+        float fv[FS4 * 4];
+        load_features<FS4>(s, fv);
+        float pv[NR];
+        s_w[n * kWRow + lane] = entry_backward<C, kDA>(fv, r1.w, dx, dy, g, amax, pg, b, pv);
+        const float tot = wave_reduce_scatter<NR>(pv, lane);
+        if (writer) pcol[j * GS] = tot;
+        if (lane == 0) L.row[wv][n] = (uint32_t)j;
+      }
+      wave_lds_sync();
+      feature_gemm<C>(s_w, L.row[wv], n, bG, s_p);
+      wave_lds_sync();
+    }
+    __syncthreads();
+    for (int t = tid; t < cnt * Q; t += NT) {
+      const int j = t / Q;
+      float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        if ((L.mask[w] >> j) & 1ull) {
+          const float4 y = reinterpret_cast<const float4*>(L.part[w])[t];
+          x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+        }
+      reinterpret_cast<float4*>(gpair)[(size_t)L.e[j] * Q + (t - j * Q)] = x;
+    }
+    __syncthreads();
+  }
+  // pairs that no pixel of the tile reached contribute nothing
+  const uint32_t nz = (tg.rend - stop) * (uint32_t)Q;
+  for (uint32_t t = (uint32_t)tid; t < nz; t += NT) {
+    const uint32_t j = t / (uint32_t)Q;
+    reinterpret_cast<float4*>(gpair)[(size_t)vals[stop + j] * Q + (t - j * (uint32_t)Q)] =
+        make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+}
+
 // Forward compositing of the batch: of the 5 + C output planes per view the
 // ones selected by mask and the view's own channel set, and, when all are
 // selected, per pixel T_final, n_last, the relative depth D' and its
-// reference t0 for the backward.
-template <int C, int PPL, int KS>
-__global__ __launch_bounds__(64) void k_render_fwd(
+// reference t0 for the backward.  One wave per 64 pixels; the waves of a tile
+// form a block (their records meet in one CU's cache) and are independent.
+template <int C, int NW>
+__global__ __launch_bounds__(64 * NW) void k_render_fwd(
     const ViewDev* __restrict__ views, int V, int N, float qcut, float amax,
-    float teps, const uint4* __restrict__ tinfo, const uint32_t* __restrict__ vals,
-    const uint32_t* __restrict__ spair,
+    float teps, const uint4* __restrict__ tinfo, const uint32_t* __restrict__ spair,
     const float4* __restrict__ rec, const float4* __restrict__ feat, float* __restrict__ out,
     float* __restrict__ tfin, uint32_t* __restrict__ nlast, float2* __restrict__ drel,
     uint32_t mask) {
@@ -525,61 +783,50 @@ __global__ __launch_bounds__(64) void k_render_fwd(
   constexpr int FS4 = (F + 4) / 4;
   constexpr int NO = 5 + C;           // output channels
   // staged entries: projection record, conic, features, one record per entry
-  __shared__ float4 s_st[KS * (2 + FS4)];
-  float4* const s_r0 = s_st;
-  float4* const s_r1 = s_st + 1;
-  float4* const s_f = s_st + 2;
-  const TileGeom tg = tile_geom(views, N, tinfo);
-  float T[PPL], acc[PPL][F + 1], pyc[PPL];
-  uint32_t nl[PPL];
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) pyc[k] = (float)(tg.py0 + k * tg.rows) + 0.5f;
-  uint32_t e_first;
-  float t0[PPL];
+  __shared__ float4 s_st[NW][64 * (2 + FS4)];
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const TileGeom tg = tile_geom(views, N, tinfo, wv);
   const uint32_t ch = (uint32_t)tg.vw->ch & mask;
   constexpr uint32_t kPlanes = ROGS_CH_RGB | ROGS_CH_SEM | ROGS_CH_D | ROGS_CH_A;
-  forward_tile<C, PPL, KS, false, true>(tg, qcut, amax, teps, vals, spair, rec, feat, s_r0, s_r1,
-                                        s_f, pyc, acc, T, nl, e_first, t0, ch);
+  Pixel<C> p;
+  forward_part<C, true>(tg, qcut, amax, teps, spair, rec, feat, s_st[wv], p, ch);
+  if (!(tg.px < tg.W && tg.py < tg.H)) return;
   const uint32_t len = tg.rend - tg.rbeg;
   const size_t HW = (size_t)tg.W * tg.H;
-  float* o = out + (size_t)NO * tg.vw->pix_off;
+  const size_t pix = (size_t)tg.py * tg.W + tg.px;
+  float* o = out + (size_t)NO * tg.vw->pix_off + pix;
+  if (ch & ROGS_CH_RGB)
 #pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int py = tg.py0 + k * tg.rows;
-    if (!(tg.px < tg.W && py < tg.H)) continue;
-    const size_t p = (size_t)py * tg.W + tg.px;
-    if (ch & ROGS_CH_RGB)
+    for (int f = 0; f < 3; ++f) o[f * HW] = p.acc[f];
+  if (ch & ROGS_CH_SEM)
 #pragma unroll
-      for (int f = 0; f < 3; ++f) o[f * HW + p] = acc[k][f];
-    if (ch & ROGS_CH_SEM)
-#pragma unroll
-      for (int f = 3; f < F; ++f) o[f * HW + p] = acc[k][f];
-    const float al = 1.0f - T[k];
-    const float t0k = t0[k] < FLT_MAX ? t0[k] : 0.0f;        // 0 where nothing contributed
-    if (ch & ROGS_CH_D) o[F * HW + p] = __builtin_fmaf(t0k, al, acc[k][F]);   // D = D' + t0 A
-    if (ch & ROGS_CH_A) o[(F + 1) * HW + p] = al;
-    if ((ch & kPlanes) == kPlanes) {
-      tfin[tg.vw->pix_off + p] = T[k];
-      nlast[tg.vw->pix_off + p] = (T[k] < teps) ? nl[k] : len;
-      drel[tg.vw->pix_off + p] = make_float2(acc[k][F], t0k);
-    }
+    for (int f = 3; f < F; ++f) o[f * HW] = p.acc[f];
+  const float al = 1.0f - p.T;
+  const float t0 = p.t0 < FLT_MAX ? p.t0 : 0.0f;           // 0 where nothing contributed
+  if (ch & ROGS_CH_D) o[F * HW] = __builtin_fmaf(t0, al, p.acc[F]);   // D = D' + t0 A
+  if (ch & ROGS_CH_A) o[(F + 1) * HW] = al;
+  if ((ch & kPlanes) == kPlanes) {
+    tfin[tg.vw->pix_off + pix] = p.T;
+    nlast[tg.vw->pix_off + pix] = (p.T < teps) ? p.nl : len;
+    drel[tg.vw->pix_off + pix] = make_float2(p.acc[F], t0);
   }
+}
+
+// Register budgets of the backward kernels of one-wave tiles: up to 8 classes,
+// 7 waves per SIMD at 16-entry staging (what its LDS block allows) and 5 at 32
+// entries (timed slightly faster than 6, the most its LDS block allows); the
+// compiler meets them without spilling in the entry loops.  Other instances
+// keep the compiler's own budget (1).
+template <int C, int NW, int KS>
+constexpr int kWavesPerEu() {
+  return (NW == 1 && C <= 8 && KS <= 32) ? (KS <= 16 ? 7 : 5) : 1;
 }
 
 // Backward compositing of the batch from the output gradient G (5 + C planes
 // per view), the outputs, T_final and n_last.
-// Register budgets of the backward kernels: with one pixel per lane and up
-// to 8 classes, 7 waves per SIMD at 16-entry staging (what its LDS block
-// allows) and 5 at 32 entries (timed slightly faster than 6, the most its
-// LDS block allows); the compiler meets them without spilling in the entry
-// loops.  Other instances keep the compiler's own budget (1).
-template <int C, int PPL, int KS>
-constexpr int kWavesPerEu() {
-  return (PPL == 1 && C <= 8 && KS <= 32) ? (KS <= 16 ? 7 : 5) : 1;
-}
-template <int C, int PPL, int KS>
-__global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, PPL, KS>()))) void k_render_bwd(
+template <int C, int NW, int KS>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, NW, KS>()))) void k_render_bwd(
     const ViewDev* __restrict__ views, int V, int N, float qcut, float amax,
     const uint4* __restrict__ tinfo, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ spair,
@@ -588,58 +835,71 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, PPL, KS>()))) void k_render_bw
     const uint32_t* __restrict__ nlast, const float2* __restrict__ drel,
     float* __restrict__ gpair) {
   constexpr int F = 3 + C;
-  constexpr int FS4 = (F + 4) / 4;
   constexpr int NO = 5 + C;
-  // staged entries: projection record, conic, features, one record per entry
-  __shared__ float4 s_st[KS * (2 + FS4)];
-  float4* const s_r0 = s_st;
-  float4* const s_r1 = s_st + 1;
-  float4* const s_f = s_st + 2;
-  __shared__ float4 s_w4[bwd_lds_floats<C, PPL>() / 4];
-  __shared__ uint32_t s_e[KS];
-  const TileGeom tg = tile_geom(views, N, tinfo);
+  __shared__ BlockLds<C, NW, KS> L;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const TileGeom tg = tile_geom(views, N, tinfo, wv);
+  if (tg.rend == tg.rbeg) return;
   const size_t HW = (size_t)tg.W * tg.H;
-  float Gv[PPL][F + 2], GO[PPL], Tf[PPL], pyc[PPL], t0[PPL];
-  uint32_t nl[PPL];
+  PixelGrad<C> pg;
+  pg.GO = 0.0f;
+  pg.Tf = 1.0f;
+  pg.nl = 0;
+  pg.t0 = 0.0f;
 #pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int py = tg.py0 + k * tg.rows;
-    pyc[k] = (float)py + 0.5f;
-    GO[k] = 0.0f;
-    Tf[k] = 1.0f;
-    nl[k] = 0;
-    t0[k] = 0.0f;
+  for (int f = 0; f < F + 2; ++f) pg.Gv[f] = 0.0f;
+  if (tg.px < tg.W && tg.py < tg.H) {
+    const size_t p = (size_t)tg.py * tg.W + tg.px;
+    const float* g = G + (size_t)NO * tg.vw->pix_off + p;
+    const float* o = out + (size_t)NO * tg.vw->pix_off + p;
+    float go = 0.0f;
 #pragma unroll
-    for (int f = 0; f < F + 2; ++f) Gv[k][f] = 0.0f;
-    if (tg.px < tg.W && py < tg.H) {
-      const size_t p = (size_t)py * tg.W + tg.px;
-      const float* g = G + (size_t)NO * tg.vw->pix_off + p;
-      const float* o = out + (size_t)NO * tg.vw->pix_off + p;
-      float go = 0.0f;
+    for (int f = 0; f < F + 2; ++f) pg.Gv[f] = g[f * HW];
 #pragma unroll
-      for (int f = 0; f < F + 2; ++f) Gv[k][f] = g[f * HW];
+    for (int f = 0; f < F; ++f) go = __builtin_fmaf(pg.Gv[f], o[f * HW], go);
+    const float2 dr = drel[tg.vw->pix_off + p];          // D' and t0 of the forward
+    go = __builtin_fmaf(pg.Gv[F], dr.x, go);
+    pg.GO = go;
+    pg.t0 = dr.y;
+    pg.Tf = tfin[tg.vw->pix_off + p];
+    pg.nl = nlast[tg.vw->pix_off + p];
+  }
+  if constexpr (NW == 1)
+    backward_tile<C, KS, true, 0>(tg, qcut, amax, vals, spair, rec, feat, L.st, L.w[0], L.e, pg,
+                                  gpair, false, 0u, nullptr);
+  else
+    backward_block<C, NW, KS, true>(tg, qcut, amax, vals, spair, rec, feat, L, pg, gpair);
+}
+
+// This tile's share of the loss and of dL/d(a, b), summed over its waves in
+// wave order.  Every wave of the block calls it.
+template <int NW>
+__device__ __forceinline__ void tile_loss(const float (&lp)[3], float* s_l, float* part) {
+  const int lane = threadIdx.x & 63;
+  const float tot = wave_reduce_scatter<3>(lp, lane);
+  const int c = rs_comp(lane, 3);
+  const bool writer = c >= 0 && (lane & rs_dup_bits(3)) == 0;
+  if constexpr (NW == 1) {
+    if (writer) part[c] = tot;
+  } else {
+    if (writer) s_l[3 * (threadIdx.x >> 6) + c] = tot;
+    __syncthreads();
+    if (threadIdx.x < 3) {
+      float t = s_l[threadIdx.x];
 #pragma unroll
-      for (int f = 0; f < F; ++f) go = __builtin_fmaf(Gv[k][f], o[f * HW], go);
-      const float2 dr = drel[tg.vw->pix_off + p];          // D' and t0 of the forward
-      go = __builtin_fmaf(Gv[k][F], dr.x, go);
-      GO[k] = go;
-      t0[k] = dr.y;
-      Tf[k] = tfin[tg.vw->pix_off + p];
-      nl[k] = nlast[tg.vw->pix_off + p];
+      for (int w = 1; w < NW; ++w) t += s_l[3 * w + threadIdx.x];
+      part[threadIdx.x] = t;
     }
   }
-  backward_tile<C, PPL, KS, true>(tg, qcut, amax, vals, spair, rec, feat, s_r0, s_r1, s_f,
-                              reinterpret_cast<float*>(s_w4), s_e, pyc, Gv, GO, Tf, nl, gpair,
-                              false, 0u, t0);
 }
 
 // The fused step's compositing: forward, the loss of Eq. 7-9 and 12 per pixel
 // (its gradient, G.O, and this tile's share of the loss and of dL/d(a, b)),
 // then the backward, in one kernel per tile.
 // Register budget as for k_render_bwd.
-template <int C, int PPL, int KS>
-__global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, PPL, KS>()))) void k_render_step(
+template <int C, int NW, int KS>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, NW, KS>()))) void k_render_step(
     const ViewDev* __restrict__ views, int V, int N, float qcut, float amax,
     float teps, const uint4* __restrict__ tinfo, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ spair,
@@ -647,115 +907,91 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, PPL, KS>()))) void k_render_st
     FusedLoss fl) {
   constexpr int F = 3 + C;
   constexpr int FS4 = (F + 4) / 4;
-  // staged entries: projection record, conic, features, one record per entry
-  __shared__ float4 s_st[KS * (2 + FS4)];
-  float4* const s_r0 = s_st;
-  float4* const s_r1 = s_st + 1;
-  float4* const s_f = s_st + 2;
-  __shared__ float4 s_w4[bwd_lds_floats<C, PPL>() / 4];
-  __shared__ uint32_t s_e[KS];
-  const int lane = threadIdx.x;
-  const TileGeom tg = tile_geom(views, N, tinfo);
-  float pyc[PPL];
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) pyc[k] = (float)(tg.py0 + k * tg.rows) + 0.5f;
-  float Gv[PPL][F + 2], GO[PPL], Tf[PPL];
-  uint32_t nl[PPL];
-  // the loss inputs of this lane's pixels (mask, target colour and label, in
+  // the forward of several waves stages in regions of their own, over the
+  // space of the waves' weight rows and partial records
+  union Lds {
+    BlockLds<C, NW, KS> b;
+    float4 f[NW == 1 ? 1 : NW][NW == 1 ? 1 : 64 * (2 + FS4)];
+  };
+  __shared__ Lds L;
+  __shared__ float s_l[3 * NW];
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const TileGeom tg = tile_geom(views, N, tinfo, NW == 1 ? 0 : wv);
+  PixelGrad<C> pg;
+  const bool in_img = tg.px < tg.W && tg.py < tg.H;
+  // the loss inputs of this lane's pixel (mask, target colour and label, in
   // parallel), requested before the forward so that their latency overlaps it
   const LossView lv = loss_view(fl.expo, fl.mcount, tg.v, fl.lam_c, fl.lam_s, fl.scale);
-  bool lmask[PPL];
-  uint32_t lab[PPL];
-  float tv[PPL][3];
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int py = tg.py0 + k * tg.rows;
-    uint32_t m = 0;
-    lab[k] = 0;
-    tv[k][0] = tv[k][1] = tv[k][2] = 0.0f;
-    if (tg.px < tg.W && py < tg.H && lv.any) {
-      const size_t p = (size_t)py * tg.W + tg.px;
-      const size_t pix = tg.vw->pix_off + p;
-      const float* t = fl.tgt + 3 * (size_t)tg.vw->pix_off + p;
-      const size_t HW = (size_t)tg.W * tg.H;
-      m = fl.mask[pix];
-      lab[k] = fl.label[pix];
-      tv[k][0] = t[0];
-      tv[k][1] = t[HW];
-      tv[k][2] = t[2 * HW];
-    }
-    lmask[k] = m != 0;
+  uint32_t m = 0, lab = 0;
+  float tv[3] = {0.0f, 0.0f, 0.0f};
+  if (in_img && lv.any) {
+    const size_t p = (size_t)tg.py * tg.W + tg.px;
+    const size_t pix = tg.vw->pix_off + p;
+    const float* t = fl.tgt + 3 * (size_t)tg.vw->pix_off + p;
+    const size_t HW = (size_t)tg.W * tg.H;
+    m = fl.mask[pix];
+    lab = fl.label[pix];
+    tv[0] = t[0];
+    tv[1] = t[HW];
+    tv[2] = t[2 * HW];
   }
+  const float wc = m != 0 ? lv.wc : 0.0f, ws = m != 0 ? lv.ws : 0.0f;
+  float* const part = fl.part + 3 * (size_t)tg.gt;
   if (tg.rend == tg.rbeg) {
     // a tile without entries: its pixels' outputs are 0 and there is nothing
     // to differentiate, so only its shares of the loss and of dL/db are
     // formed (dL/da is 0 at a zero output)
     float l = 0.0f, dbl = 0.0f;
-#pragma unroll
-    for (int k = 0; k < PPL; ++k)
-      pixel_loss_empty<C>(tv[k], lmask[k] ? lv.wc : 0.0f, lmask[k] ? lv.ws : 0.0f, lv.ea, lv.b,
-                          l, dbl);
+    pixel_loss_empty<C>(tv, wc, ws, lv.ea, lv.b, l, dbl);
     const float lp[3] = {l, 0.0f, dbl};
-    const float tot = wave_reduce_scatter<3>(lp, lane);
-    const int c = rs_comp(lane, 3);
-    if (c >= 0 && (lane & rs_dup_bits(3)) == 0) fl.part[3 * (size_t)tg.gt + c] = tot;
+    tile_loss<NW>(lp, s_l, part);
     return;
   }
+  // the footprint weights of the list's first 16 entries, kept from the
+  // forward for the backward where the register budget has room for them
+  // (one-wave tiles; up to 8 classes only with 32-entry staging, since
+  // at 16 they would spill; with 16 classes the kernel runs 3 waves per
+  // SIMD with or without them)
+  constexpr int kG = (NW == 1 && (C > 8 || KS == 32)) ? 16 : 0;
+  float gsv[16];
+  uint32_t e_first = 0;
+  Pixel<C> px;
+  constexpr uint32_t kCh = ROGS_CH_RGB | ROGS_CH_SEM;
+  if constexpr (NW == 1)
+    forward_tile<C, KS, kG>(tg, qcut, amax, teps, vals, spair, rec, feat, L.b.st, px, e_first, kCh,
+                            gsv);
+  else
+    forward_part<C, false>(tg, qcut, amax, teps, spair, rec, feat, L.f[wv], px, kCh);
+  // loss epilogue: dL/dO and G.O per pixel, this tile's loss partials
+  const uint32_t len = tg.rend - tg.rbeg;
+  float l = 0.0f, dal = 0.0f, dbl = 0.0f;
   {
-    float T[PPL], acc[PPL][F + 1];
-    uint32_t nlf[PPL];
-    uint32_t e_first = 0;
-    float t0[PPL];          // not used: the fused loss has no depth term
+    float g[F];
+    // every lane evaluates the loss; a pixel outside the mask or the image
+    // has zero weights, so its gradient and loss terms are +-0
+    pixel_loss<C>(px.acc, tv, lab, wc, ws, lv.ea, lv.b, g, l, dal, dbl);
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) t0[k] = 0.0f;
-    // the footprint weights of the list's first 16 entries, kept from the
-    // forward for the backward where the register budget has room for them
-    // (one pixel per lane; up to 8 classes only with 32-entry staging, since
-    // at 16 they would spill; with 16 classes the kernel runs 3 waves per
-    // SIMD with or without them)
-    constexpr int kG = (PPL == 1 && (C > 8 || KS == 32)) ? 16 : 0;
-    float gsv[16];
-    forward_tile<C, PPL, KS, true, false, kG>(tg, qcut, amax, teps, vals, spair, rec, feat, s_r0,
-                                              s_r1, s_f, pyc, acc, T, nlf, e_first, t0,
-                                              ROGS_CH_RGB | ROGS_CH_SEM, gsv);
-    // loss epilogue: dL/dO and G.O per pixel, this tile's loss partials
-    const uint32_t len = tg.rend - tg.rbeg;
-    float l = 0.0f, dal = 0.0f, dbl = 0.0f;
+    for (int f = 0; f < F; ++f) pg.Gv[f] = g[f];
+    pg.Gv[F] = 0.0f;         // the fused loss has no depth or alpha term
+    pg.Gv[F + 1] = 0.0f;
+    // G.O over the composited channels, in the same form as the stand-alone
+    // backward so that both round alike (its depth term adds 0 * D' = +0)
+    float go = 0.0f;
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-      const int py = tg.py0 + k * tg.rows;
-      float g[F];
-      // every lane evaluates the loss; a pixel outside the mask or the image
-      // has zero weights, so its gradient and loss terms are +-0
-      pixel_loss<C>(acc[k], tv[k], lab[k], lmask[k] ? lv.wc : 0.0f, lmask[k] ? lv.ws : 0.0f,
-                    lv.ea, lv.b, g, l, dal, dbl);
-#pragma unroll
-      for (int f = 0; f < F; ++f) Gv[k][f] = g[f];
-      Gv[k][F] = 0.0f;         // the fused loss has no depth or alpha term
-      Gv[k][F + 1] = 0.0f;
-      // G.O over the composited channels, in the same form as the stand-alone
-      // backward so that both round alike (its depth term adds 0 * D' = +0)
-      float go = 0.0f;
-#pragma unroll
-      for (int f = 0; f < F; ++f) go = __builtin_fmaf(Gv[k][f], acc[k][f], go);
-      const bool in_img = tg.px < tg.W && py < tg.H;
-      const float tf = in_img ? T[k] : 1.0f;
-      const uint32_t nlk = in_img ? ((T[k] < teps) ? nlf[k] : len) : 0u;
-      GO[k] = go;
-      Tf[k] = tf;
-      nl[k] = nlk;
-    }
-    {
-      const float lp[3] = {l, dal, dbl};
-      const float tot = wave_reduce_scatter<3>(lp, lane);
-      const int c = rs_comp(lane, 3);
-      if (c >= 0 && (lane & rs_dup_bits(3)) == 0) fl.part[3 * (size_t)tg.gt + c] = tot;
-    }
-    // the fused loss has no depth or alpha term: their gradient rows are zero
-    backward_tile<C, PPL, KS, false, kG>(tg, qcut, amax, vals, spair, rec, feat, s_r0, s_r1,
-                                         s_f, reinterpret_cast<float*>(s_w4), s_e, pyc, Gv, GO,
-                                         Tf, nl, gpair, len <= (uint32_t)KS, e_first, t0, gsv);
+    for (int f = 0; f < F; ++f) go = __builtin_fmaf(pg.Gv[f], px.acc[f], go);
+    pg.GO = go;
+    pg.Tf = in_img ? px.T : 1.0f;
+    pg.nl = in_img ? ((px.T < teps) ? px.nl : len) : 0u;
+    pg.t0 = 0.0f;            // not used without a depth term
   }
+  const float lp[3] = {l, dal, dbl};
+  tile_loss<NW>(lp, s_l, part);   // its barrier also ends the forward's use of L
+  // the fused loss has no depth or alpha term: their gradient rows are zero
+  if constexpr (NW == 1)
+    backward_tile<C, KS, false, kG>(tg, qcut, amax, vals, spair, rec, feat, L.b.st, L.b.w[0],
+                                    L.b.e, pg, gpair, len <= (uint32_t)KS, e_first, gsv);
+  else
+    backward_block<C, NW, KS, false>(tg, qcut, amax, vals, spair, rec, feat, L.b, pg, gpair);
 }
 
 // Work counts of a rendered batch (diagnostics): per pixel, the list entries
@@ -763,7 +999,7 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, PPL, KS>()))) void k_render_st
 // those, the ones whose 3-sigma test passes.  Summed over the batch into
 // counts[0] (evaluated) and counts[1] (contributing) with 64-bit atomics.
 __global__ __launch_bounds__(64) void k_count_work(
-    const ViewDev* __restrict__ views, int V, int ppl, float qcut,
+    const ViewDev* __restrict__ views, int V, int nw, float qcut,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ pslot, const float4* __restrict__ rec,
     const uint32_t* __restrict__ nlast, unsigned long long* __restrict__ counts) {
@@ -783,7 +1019,7 @@ __global__ __launch_bounds__(64) void k_count_work(
   for (int k = 0; k < 4; ++k) {
     const int py = ty * th + lane / tw + k * rows;
     pyc[k] = (float)py + 0.5f;
-    nl[k] = (k < ppl && px < vw.w && py < vw.h) ? nlast[vw.pix_off + (size_t)py * vw.w + px] : 0u;
+    nl[k] = (k < nw && px < vw.w && py < vw.h) ? nlast[vw.pix_off + (size_t)py * vw.w + px] : 0u;
     maxn = max(maxn, nl[k]);
   }
   for (int o = 32; o > 0; o >>= 1) maxn = max(maxn, (uint32_t)__shfl_xor((int)maxn, o, 64));
@@ -812,21 +1048,21 @@ __global__ __launch_bounds__(64) void k_count_work(
   }
 }
 
-template <int C, int PPL, int KS>
+template <int C, int NW>
 void fwd_launch(const Layout& L, void* ws, float* out, uint32_t mask, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_fwd<C, PPL, KS>), dim3((unsigned)L.total_tiles), dim3(64), 0, st,
+  hipLaunchKernelGGL((k_render_fwd<C, NW>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0, st,
                      at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
-                     L.t_eps, at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_vals),
+                     L.t_eps, at<const uint4>(ws, L.o_tinfo),
                      at<const uint32_t>(ws, L.o_spair),
                      at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out,
                      at<float>(ws, L.o_tfin), at<uint32_t>(ws, L.o_nlast),
                      at<float2>(ws, L.o_drel), mask);
 }
 
-template <int C, int PPL, int KS>
+template <int C, int NW, int KS>
 void bwd_launch(const Layout& L, void* ws, const float* out, const float* G, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_bwd<C, PPL, KS>), dim3((unsigned)L.total_tiles), dim3(64), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
+  hipLaunchKernelGGL((k_render_bwd<C, NW, KS>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0,
+                     st, at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
                      at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_vals),
                      at<const uint32_t>(ws, L.o_spair),
                      at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out, G,
@@ -834,10 +1070,10 @@ void bwd_launch(const Layout& L, void* ws, const float* out, const float* G, hip
                      at<const float2>(ws, L.o_drel), at<float>(ws, L.o_gpair));
 }
 
-template <int C, int PPL, int KS>
+template <int C, int NW, int KS>
 void step_launch(const Layout& L, void* ws, const FusedLoss& fl, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_step<C, PPL, KS>), dim3((unsigned)L.total_tiles), dim3(64), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
+  hipLaunchKernelGGL((k_render_step<C, NW, KS>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0,
+                     st, at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
                      L.t_eps, at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_vals),
                      at<const uint32_t>(ws, L.o_spair),
                      at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat),
@@ -845,29 +1081,32 @@ void step_launch(const Layout& L, void* ws, const FusedLoss& fl, hipStream_t st)
 }
 
 // which: 0 forward, 1 backward, 2 fused step
-template <int C, int PPL, int KS>
-void launch_one(const Layout& L, void* ws, const float* out, const float* G, float* outw,
-                const FusedLoss* fl, int which, uint32_t mask, hipStream_t st) {
-  if (which == 0) fwd_launch<C, PPL, KS>(L, ws, outw, mask, st);
-  else if (which == 1) bwd_launch<C, PPL, KS>(L, ws, out, G, st);
-  else step_launch<C, PPL, KS>(L, ws, *fl, st);
+template <int C, int NW, int KS>
+void launch_one(const Layout& L, void* ws, const float* out, const float* G, const FusedLoss* fl,
+                int which, hipStream_t st) {
+  if (which == 1) bwd_launch<C, NW, KS>(L, ws, out, G, st);
+  else step_launch<C, NW, KS>(L, ws, *fl, st);
 }
 
-template <int C, int PPL>
+template <int C, int NW>
 int dispatch_stage(const Layout& L, void* ws, const float* out, const float* G, float* outw,
                    const FusedLoss* fl, int which, uint32_t mask, hipStream_t st) {
+  if (which == 0) {
+    fwd_launch<C, NW>(L, ws, outw, mask, st);
+    return 0;
+  }
   switch (L.stage) {
-    case 16: launch_one<C, PPL, 16>(L, ws, out, G, outw, fl, which, mask, st); return 0;
-    case 32: launch_one<C, PPL, 32>(L, ws, out, G, outw, fl, which, mask, st); return 0;
-    case 64: launch_one<C, PPL, 64>(L, ws, out, G, outw, fl, which, mask, st); return 0;
+    case 16: launch_one<C, NW, 16>(L, ws, out, G, fl, which, st); return 0;
+    case 32: launch_one<C, NW, 32>(L, ws, out, G, fl, which, st); return 0;
+    case 64: launch_one<C, NW, 64>(L, ws, out, G, fl, which, st); return 0;
     default: return -1;
   }
 }
 
 template <int C>
-int dispatch_ppl(const Layout& L, void* ws, const float* out, const float* G, float* outw,
-                 const FusedLoss* fl, int which, uint32_t mask, hipStream_t st) {
-  switch (L.ppl) {
+int dispatch_waves(const Layout& L, void* ws, const float* out, const float* G, float* outw,
+                   const FusedLoss* fl, int which, uint32_t mask, hipStream_t st) {
+  switch (L.nw) {
     case 1: return dispatch_stage<C, 1>(L, ws, out, G, outw, fl, which, mask, st);
     case 2: return dispatch_stage<C, 2>(L, ws, out, G, outw, fl, which, mask, st);
     case 4: return dispatch_stage<C, 4>(L, ws, out, G, outw, fl, which, mask, st);
@@ -878,15 +1117,15 @@ int dispatch_ppl(const Layout& L, void* ws, const float* out, const float* G, fl
 int dispatch(const Layout& L, void* ws, const float* out, const float* G, float* outw,
              const FusedLoss* fl, int which, uint32_t mask, hipStream_t st) {
   switch (L.C) {
-    case 1: return dispatch_ppl<1>(L, ws, out, G, outw, fl, which, mask, st);
-    case 2: return dispatch_ppl<2>(L, ws, out, G, outw, fl, which, mask, st);
-    case 3: return dispatch_ppl<3>(L, ws, out, G, outw, fl, which, mask, st);
-    case 4: return dispatch_ppl<4>(L, ws, out, G, outw, fl, which, mask, st);
-    case 5: return dispatch_ppl<5>(L, ws, out, G, outw, fl, which, mask, st);
-    case 6: return dispatch_ppl<6>(L, ws, out, G, outw, fl, which, mask, st);
-    case 7: return dispatch_ppl<7>(L, ws, out, G, outw, fl, which, mask, st);
-    case 8: return dispatch_ppl<8>(L, ws, out, G, outw, fl, which, mask, st);
-    case 16: return dispatch_ppl<16>(L, ws, out, G, outw, fl, which, mask, st);
+    case 1: return dispatch_waves<1>(L, ws, out, G, outw, fl, which, mask, st);
+    case 2: return dispatch_waves<2>(L, ws, out, G, outw, fl, which, mask, st);
+    case 3: return dispatch_waves<3>(L, ws, out, G, outw, fl, which, mask, st);
+    case 4: return dispatch_waves<4>(L, ws, out, G, outw, fl, which, mask, st);
+    case 5: return dispatch_waves<5>(L, ws, out, G, outw, fl, which, mask, st);
+    case 6: return dispatch_waves<6>(L, ws, out, G, outw, fl, which, mask, st);
+    case 7: return dispatch_waves<7>(L, ws, out, G, outw, fl, which, mask, st);
+    case 8: return dispatch_waves<8>(L, ws, out, G, outw, fl, which, mask, st);
+    case 16: return dispatch_waves<16>(L, ws, out, G, outw, fl, which, mask, st);
     default: return -1;
   }
 }
@@ -908,7 +1147,7 @@ int launch_render_bwd(const Layout& L, void* ws, const rogs_surfels*, const floa
 void launch_count_work(const Layout& L, void* ws, unsigned long long* counts, hipStream_t st) {
   if (L.total_tiles <= 0) return;
   hipLaunchKernelGGL(k_count_work, dim3((unsigned)L.total_tiles), dim3(64), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.ppl, L.q_cut,
+                     at<const ViewDev>(ws, L.o_views), L.V, L.nw, L.q_cut,
                      at<const uint2>(ws, L.o_ranges), at<const uint32_t>(ws, L.o_vals),
                      at<const uint32_t>(ws, L.o_pslot), at<const float4>(ws, L.o_rec),
                      at<const uint32_t>(ws, L.o_nlast), counts);

@@ -57,7 +57,7 @@ inline int grad_stride(int C) { return (int)grad_stride_c(C); }
 // Layout of one batch inside the caller's workspace (byte offsets).
 struct Layout {
   int32_t N = 0, C = 0, V = 0;
-  int32_t tw = 16, th = 16, ppl = 4;   // the options' tile shape (views may differ, same area)
+  int32_t tw = 16, th = 16, nw = 4;    // the options' tile shape (views may differ, same area), its waves
   int32_t stage = 32;                   // list entries staged in LDS per batch
   int32_t FS = 0, GS = 0;
   int32_t nb = 0;              // blocks of kProjBlock surfels
