@@ -66,8 +66,6 @@ struct rogs_ctx {
     int64_t launched = 0;                // steps launched so far
     int last = 0;                        // buffer of the last launched step
     hipStream_t cap_stream = nullptr;    // capture happens here (the null stream cannot be captured)
-    hipStream_t side = nullptr;          // the long lists' depth sort, beside the short ones
-    hipEvent_t fork = nullptr, join = nullptr;
   } fz;
 };
 
@@ -452,9 +450,6 @@ void rogs_destroy(rogs_ctx* c) {
     if (c->fz.done[k]) (void)hipEventDestroy(c->fz.done[k]);
   }
   if (c->fz.cap_stream) (void)hipStreamDestroy(c->fz.cap_stream);
-  if (c->fz.side) (void)hipStreamDestroy(c->fz.side);
-  if (c->fz.fork) (void)hipEventDestroy(c->fz.fork);
-  if (c->fz.join) (void)hipEventDestroy(c->fz.join);
   if (!c->recs.empty()) (void)hipEventSynchronize(c->recs.back().b);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->stage_pending) (void)hipEventSynchronize(c->stage_evt);
@@ -604,7 +599,7 @@ int rogs_bin_sort(rogs_ctx* c, void* ws, int64_t* n_pairs_out, uint32_t flags, v
   rogs::launch_binning(L, ws, n_host, n_vis, st);
   prof_end(c, st);
   prof_begin(c, 4, st);
-  (void)rogs::launch_ranges(L, ws, st);
+  rogs::launch_ranges(L, ws, st);
   prof_end(c, st);
   r = check_launch(c, "rogs_bin_sort");
   if (r != ROGS_OK) return r;
@@ -870,9 +865,8 @@ int fused_sequence(rogs_ctx* c, Layout& L, const rogs_train_state* t, const rogs
   rogs::launch_binning(L, ws, -1, -1, st, true);
   prof_end(c, st);
   prof_begin(c, 4, st);
-  hipError_t e = rogs::launch_ranges(L, ws, st, c->fz.side, c->fz.fork, c->fz.join);
+  rogs::launch_ranges(L, ws, st);
   prof_end(c, st);
-  if (e != hipSuccess) return hip_fail(c, e, "rogs_step_fused: depth sort streams");
   rogs::FusedLoss fl;
   fl.tgt = tg->rgb;
   fl.label = tg->label;
@@ -1009,12 +1003,6 @@ int rogs_step_fused(rogs_ctx* c, const rogs_train_state* t, const rogs_camera* c
     e = hipMemcpyAsync(rogs::at<void>(ws, L.o_views), F.stage[p], vbytes + fbytes,
                        hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(c, e, "rogs_step_fused: camera table");
-  }
-  if (!F.side) {
-    e = hipStreamCreateWithFlags(&F.side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&F.fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&F.join, hipEventDisableTiming);
-    if (e != hipSuccess) return hip_fail(c, e, "rogs_step_fused: side stream");
   }
   if (eager) {
     Layout Lr = L;

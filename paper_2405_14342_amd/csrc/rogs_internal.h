@@ -654,12 +654,8 @@ void launch_scan_part(const Layout& L, void* ws, hipStream_t st, bool mask_parts
 // zeroed by the projection launch.
 void launch_binning(const Layout& L, void* ws, int64_t n_pairs, int64_t n_vis, hipStream_t st,
                     bool counts_cleared = false);
-// Each tile's list by depth.  With a side stream (and two events) the lists
-// longer than 64 entries are sorted there, concurrently with the short ones,
-// and st waits for them before returning; the events' record / wait results
-// are returned.
-hipError_t launch_ranges(const Layout& L, void* ws, hipStream_t st, hipStream_t side = nullptr,
-                         hipEvent_t fork = nullptr, hipEvent_t join = nullptr);
+// Each tile's list by depth.
+void launch_ranges(const Layout& L, void* ws, hipStream_t st);
 void launch_count_work(const Layout& L, void* ws, unsigned long long* counts, hipStream_t st);
 int64_t elev_reg_blocks(int n);
 void launch_elev_reg(int n, const float* z, const int32_t* nbr, float lam_s, const float* zbar,

@@ -522,46 +522,146 @@ __device__ __forceinline__ void wave_sort_list(uint32_t beg, uint32_t len,
   }
 }
 
-// Lists of 1 to 511 entries.  The launch order groups the tiles by the bit
-// length bl of their list length.  For bl <= 6 a wave takes 64 / 2^bl
-// consecutive tiles of one group, each on a segment of 2^bl lanes, and sorts
-// every segment with one bitonic network over (key, e) (the e of a tile are
-// distinct, so the order is strict); for bl = 7, 8, 9 (64 to 511 entries) a
-// wave takes one tile and holds 2, 4 or 8 entries per lane (wave_sort_list).
-// Work items (waves) of a group: ceil(tiles / tiles per wave); the blocks
-// stride over all groups' items, longest lists first.  Lists of 512 or more
-// entries are left to k_tile_sort_long.
-constexpr uint32_t kWaveSortMax = 511;
-
-__global__ __launch_bounds__(64) void k_tile_sort_short(const uint4* __restrict__ tinfo,
-                                                        const uint32_t* __restrict__ bucket_tot,
-                                                        uint32_t* __restrict__ vals,
-                                                        const uint32_t* __restrict__ pslot,
-                                                        const uint32_t* __restrict__ pdep,
-                                                        uint32_t* __restrict__ spair) {
-  // launch-order buckets: key 15 - bl, so bucket d holds bit length 15 - d
-  __shared__ uint32_t s_start[16], s_cnt[16], s_items[16];
-  const int lane = threadIdx.x;
-  if (lane < 16) s_cnt[lane] = bucket_tot[lane];
-  __syncthreads();
-  if (lane == 0) {
-    uint32_t st = 0;
-    for (int d = 0; d < 16; ++d) {
-      const int bl = 15 - d;
-      s_start[d] = st;
-      st += s_cnt[d];
-      s_items[d] = 0u;
-      if (bl >= 1 && bl <= 9) {
-        const uint32_t per = bl >= 6 ? 1u : 64u >> bl;         // tiles per wave
-        s_items[d] = (s_cnt[d] + per - 1u) / per;
-      }
-    }
+// A run of up to 256 R entries of one list, sorted by one block of 4 waves:
+// each wave sorts 64 R entries in registers, then two rounds of merging in LDS
+// double the runs, every element finding its place in the partner run by a
+// binary search (an element of the even run goes before equal ones of the odd
+// run, which only padding has).  Leaves element idx[r] = sorted position and v
+// = (t_z bits, e) in registers, and the sorted run in s.
+template <int R>
+__device__ __forceinline__ void block_sort_run(uint32_t beg, uint32_t cnt,
+                                               const uint32_t* __restrict__ vals,
+                                               const uint32_t* __restrict__ pdep,
+                                               unsigned long long* s) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t key[R], e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = (uint32_t)(wv * 64 * R + r * 64 + lane);
+    e[r] = key[r] = 0xffffffffu;
+    if (i < cnt) e[r] = vals[beg + i];
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if ((uint32_t)(wv * 64 * R + r * 64 + lane) < cnt) key[r] = pdep[e[r]];
+  wave_sort_regs<R>(key, e, lane);
+  unsigned long long v[R];
+  uint32_t idx[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    v[r] = (unsigned long long)key[r] << 32 | e[r];
+    idx[r] = (uint32_t)(wv * 64 * R + r * 64 + lane);
+    s[idx[r]] = v[r];
   }
   __syncthreads();
-  uint32_t total = 0;
-  for (int d = 0; d < 16; ++d) total += s_items[d];
-  for (uint32_t w = blockIdx.x; w < total; w += gridDim.x) {
+#pragma unroll
+  for (uint32_t len = 64u * R; len < 256u * R; len <<= 1) {
+    uint32_t lo[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) lo[r] = 0u;
+#pragma unroll
+    for (uint32_t h = len >> 1; h > 0u; h >>= 1)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t p0 = (idx[r] & ~(len - 1u)) ^ len;      // the partner run
+        const unsigned long long x = s[p0 + lo[r] + h - 1u];
+        if ((idx[r] & len) ? x <= v[r] : x < v[r]) lo[r] += h;
+      }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t p0 = (idx[r] & ~(len - 1u)) ^ len;
+      const unsigned long long x = s[p0 + lo[r]];
+      if ((idx[r] & len) ? x <= v[r] : x < v[r]) lo[r] += 1u;
+      idx[r] = (idx[r] & ~len) + lo[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[idx[r]] = v[r];
+    __syncthreads();
+  }
+}
+
+// The depth order of every list, by work items taken in turn by blocks of 4
+// waves, longest lists first.  The launch order groups the tiles by the bit
+// length bl of their list length.
+//   bl >= 10 (512 entries and more): a block sorts one run of up to
+//     kSortRun entries (block_sort_run).  A list of one run is then in order;
+//     the runs of a longer one go to (tmpk, tmpv) for k_tile_merge.
+//   bl = 7, 8, 9 (64 to 511): a wave takes one tile and holds 2, 4 or 8
+//     entries per lane (wave_sort_list).
+//   bl <= 6: a wave takes 64 / 2^bl consecutive tiles of one group, each on a
+//     segment of 2^bl lanes, and sorts every segment with one bitonic network
+//     over (key, e) (the e of a tile are distinct, so the order is strict).
+// A list of n > kSortRun entries is n / kSortRun runs sorted side by side and
+// merged by one binary search per element and foreign run.  Measured against
+// one block per list (an LDS bitonic network up to 4096 entries, beyond that
+// every entry ranked against all others) beside a launch for the short lists:
+// 12 views of 397 x 223 over 400k surfels (lists of thousands) 6792 + 23 ->
+// 32 + 41 us, a 640 x 360 view of 3M surfels 102 + 22 -> 21 + 8 us, 24 views
+// over 800k (few lists above 511) 135 with 53 beside it -> 145 + 5 us.  Runs
+// of 2048 entries (8 per thread) would take 104 registers instead of 60 and
+// halve the waves that the short lists, the bulk of the work, run with.
+constexpr uint32_t kSortRun = 1024;
+constexpr int kSortBlocks = 4096;
+
+// Runs of a list in group bl, counted from its bit length (bl = 15 holds every
+// longer list too: its items then stride over the runs).
+__device__ __forceinline__ uint32_t sort_runs(int bl) { return bl <= 10 ? 1u : 1u << (bl - 10); }
+
+__global__ __launch_bounds__(256) void k_tile_sort(const uint4* __restrict__ tinfo,
+                                                   const uint32_t* __restrict__ bucket_tot,
+                                                   uint32_t* __restrict__ vals,
+                                                   const uint32_t* __restrict__ pslot,
+                                                   const uint32_t* __restrict__ pdep,
+                                                   uint32_t* __restrict__ spair,
+                                                   uint32_t* __restrict__ tmpk,
+                                                   uint32_t* __restrict__ tmpv) {
+  // launch-order buckets: key 15 - bl, so bucket d holds bit length 15 - d
+  __shared__ uint32_t s_start[16], s_cnt[16], s_items[16];
+  __shared__ unsigned long long s_run[kSortRun];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid < 16) s_cnt[tid] = bucket_tot[tid];
+  __syncthreads();
+  if (tid < 16) {
+    uint32_t st = 0;
+    for (int d = 0; d < tid; ++d) st += s_cnt[d];
+    const int bl = 15 - tid;
+    s_start[tid] = st;
+    const uint32_t per = bl >= 6 ? 1u : 64u >> bl;              // tiles per wave
+    s_items[tid] = bl >= 10 ? s_cnt[tid] * sort_runs(bl)
+                            : bl >= 1 ? (s_cnt[tid] + per - 1u) / per : 0u;
+  }
+  __syncthreads();
+  uint32_t nlong = 0, nshort = 0;
+  for (int d = 0; d < 16; ++d) (d <= 5 ? nlong : nshort) += s_items[d];
+  for (uint32_t w = blockIdx.x; w < nlong; w += gridDim.x) {
     int d = 0;
+    uint32_t wi = w;
+    while (wi >= s_items[d]) { wi -= s_items[d]; ++d; }
+    const uint32_t per = sort_runs(15 - d);
+    const uint4 ti = tinfo[s_start[d] + wi / per];
+    const uint32_t len = ti.z - ti.y;
+    for (uint32_t o = (wi % per) * kSortRun; o < len; o += per * kSortRun) {
+      const uint32_t beg = ti.y + o, cnt = min(kSortRun, len - o);
+      block_sort_run<(int)(kSortRun / 256u)>(beg, cnt, vals, pdep, s_run);
+      for (uint32_t i = (uint32_t)tid; i < cnt; i += 256u) {
+        const unsigned long long x = s_run[i];
+        const uint32_t e = (uint32_t)x;
+        if (len <= kSortRun) {
+          vals[beg + i] = e;
+          spair[beg + i] = pslot[e];
+        } else {
+          tmpk[beg + i] = (uint32_t)(x >> 32);
+          tmpv[beg + i] = e;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  const uint32_t skip = nlong % gridDim.x;      // blocks that took one long item more
+  const uint32_t first = (blockIdx.x + gridDim.x - skip) % gridDim.x;
+  for (uint32_t w = first * 4u + (uint32_t)wv; w < nshort; w += gridDim.x * 4u) {
+    int d = 6;
     uint32_t wi = w;
     while (wi >= s_items[d]) { wi -= s_items[d]; ++d; }
     const int bl = 15 - d;
@@ -609,108 +709,51 @@ __global__ __launch_bounds__(64) void k_tile_sort_short(const uint4* __restrict_
   }
 }
 
-// Lists of more than kWaveSortMax entries, taken in launch order (longest
-// first, so a block stops at the first shorter list): up to kLongSort
-// entries in an LDS bitonic network; longer lists by ranking every entry
-// against all others through the free sort buffers (quadratic, for rare
-// extreme lists).
-constexpr int kLongSort = 4096;
-constexpr int kLongBlocks = 4096;
-constexpr int kShortBlocks = 16384;
-
-__global__ __launch_bounds__(256) void k_tile_sort_long(const uint4* __restrict__ tinfo, int64_t T,
-                                                        uint32_t* __restrict__ vals,
-                                                        const uint32_t* __restrict__ pslot,
-                                                        const uint32_t* __restrict__ pdep,
-                                                        uint32_t* __restrict__ spair,
-                                                        uint32_t* __restrict__ tmpk,
-                                                        uint32_t* __restrict__ tmpv) {
-  __shared__ uint32_t s_k[kLongSort];
-  __shared__ uint32_t s_i[kLongSort];   // e of each entry
-  const int tid = threadIdx.x;
-  for (int64_t b = blockIdx.x; b < T; b += gridDim.x) {
-    const uint4 ti = tinfo[b];
-    const uint32_t beg = ti.y, len = ti.z - ti.y;
-    if (len <= kWaveSortMax) break;
-    if (len <= (uint32_t)kLongSort) {
-      uint32_t P = 128u;
-      while (P < len) P <<= 1;
-      for (uint32_t i = tid; i < P; i += 256u) {
-        uint32_t key = 0xffffffffu, e = 0xffffffffu;
-        if (i < len) {
-          e = vals[beg + i];
-          key = pdep[e];
-        }
-        s_k[i] = key;
-        s_i[i] = e;
-      }
-      __syncthreads();
-      // distances below 64 stay inside a wave's 64-element chunk: those steps
-      // run on registers with cross-lane exchanges, the longer ones on LDS
-      const int lane = tid & 63, wave = tid >> 6;
-      auto chunk_steps = [&](uint32_t kfrom, uint32_t kto) {   // stages kfrom ... kto
-        for (uint32_t c = (uint32_t)wave; c < (P >> 6); c += 4u) {
-          const uint32_t gi = (c << 6) | (uint32_t)lane;
-          uint32_t key = s_k[gi], idx = s_i[gi];
-          for (uint32_t kk = kfrom; kk <= kto; kk <<= 1) {
-            for (uint32_t j = min(kk >> 1, 32u); j > 0u; j >>= 1) {
-              const uint32_t ok = (uint32_t)__shfl_xor((int)key, (int)j, 64);
-              const uint32_t oi = (uint32_t)__shfl_xor((int)idx, (int)j, 64);
-              const bool keep_min = (((uint32_t)lane & j) == 0u) == ((gi & kk) == 0u);
-              if (keep_min == key_less(ok, oi, key, idx)) {
-                key = ok;
-                idx = oi;
-              }
-            }
+// The lists of more than kSortRun entries, whose runs k_tile_sort left in
+// (tmpk, tmpv): an element's place is its place in its own run plus, for every
+// other run, the entries there that are less.  Work items of 256 elements.
+__global__ __launch_bounds__(256) void k_tile_merge(const uint4* __restrict__ tinfo,
+                                                    const uint32_t* __restrict__ bucket_tot,
+                                                    const uint32_t* __restrict__ pslot,
+                                                    const uint32_t* __restrict__ tmpk,
+                                                    const uint32_t* __restrict__ tmpv,
+                                                    uint32_t* __restrict__ vals,
+                                                    uint32_t* __restrict__ spair) {
+  constexpr uint32_t kPerRun = kSortRun / 256u;
+  uint32_t st = 0, w0 = 0;
+  for (int d = 0; d <= 4; ++d) {                 // bl = 15 ... 11
+    const uint32_t cnt = bucket_tot[d];
+    const uint32_t per = sort_runs(15 - d) * kPerRun, items = cnt * per;
+    // this block's items of the group: w0 + k for the k that keep the stride
+    const uint32_t skip = w0 % gridDim.x;
+    const uint32_t k0 = (blockIdx.x + gridDim.x - skip) % gridDim.x;
+    for (uint32_t k = k0; k < items; k += gridDim.x) {
+      const uint4 ti = tinfo[st + k / per];
+      const uint32_t len = ti.z - ti.y;
+      if (len <= kSortRun) continue;
+      const uint32_t* tk = tmpk + ti.y;
+      const uint32_t* te = tmpv + ti.y;
+      for (uint32_t i = (k % per) * 256u + threadIdx.x; i < len; i += per * 256u) {
+        const uint32_t key = tk[i], e = te[i];
+        const uint32_t own = i / kSortRun;
+        uint32_t pos = i - own * kSortRun;
+        for (uint32_t r = 0; r * kSortRun < len; ++r) {
+          if (r == own) continue;
+          uint32_t lo = r * kSortRun, hi = min(lo + kSortRun, len);
+          const uint32_t b0 = lo;
+          while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            const uint32_t mk = tk[mid];
+            if (mk < key || (mk == key && te[mid] < e)) lo = mid + 1u; else hi = mid;
           }
-          s_k[gi] = key;
-          s_i[gi] = idx;
+          pos += lo - b0;
         }
-        __syncthreads();
-      };
-      chunk_steps(2u, 64u);
-      for (uint32_t k = 128u; k <= P; k <<= 1) {
-        for (uint32_t j = k >> 1; j >= 64u; j >>= 1) {
-          for (uint32_t t = tid; t < (P >> 1); t += 256u) {
-            const uint32_t i = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));   // lower element
-            const uint32_t p = i | j;
-            const uint32_t ka = s_k[i], ia = s_i[i], kb = s_k[p], ib = s_i[p];
-            const bool up = (i & k) == 0u;
-            if (up == key_less(kb, ib, ka, ia)) {
-              s_k[i] = kb; s_i[i] = ib;
-              s_k[p] = ka; s_i[p] = ia;
-            }
-          }
-          __syncthreads();
-        }
-        chunk_steps(k, k);
+        vals[ti.y + pos] = e;
+        spair[ti.y + pos] = pslot[e];
       }
-      for (uint32_t rk = tid; rk < len; rk += 256u) {
-        const uint32_t e = s_i[rk];
-        vals[beg + rk] = e;
-        spair[beg + rk] = pslot[e];
-      }
-      __syncthreads();
-    } else {
-      for (uint32_t i = tid; i < len; i += 256u) {
-        tmpk[beg + i] = pdep[vals[beg + i]];
-      }
-      __syncthreads();
-      for (uint32_t i = tid; i < len; i += 256u) {
-        const uint32_t ki = tmpk[beg + i], ei = vals[beg + i];
-        uint32_t rank = 0u;
-        for (uint32_t j = 0; j < len; ++j)
-          rank += key_less(tmpk[beg + j], vals[beg + j], ki, ei) ? 1u : 0u;
-        tmpv[beg + rank] = ei;
-      }
-      __syncthreads();
-      for (uint32_t rk = tid; rk < len; rk += 256u) {
-        const uint32_t e = tmpv[beg + rk];
-        vals[beg + rk] = e;
-        spair[beg + rk] = pslot[e];
-      }
-      __syncthreads();
     }
+    st += cnt;
+    w0 += items;
   }
 }
 
@@ -916,33 +959,22 @@ void launch_binning(const Layout& L, void* ws, int64_t n_pairs, int64_t n_vis, h
                        rank, tstart, n_emit, p_grid, L.cap, at<uint32_t>(ws, L.o_vals));
 }
 
-hipError_t launch_ranges(const Layout& L, void* ws, hipStream_t st, hipStream_t side,
-                         hipEvent_t fork, hipEvent_t join) {
-  // each tile's list by depth, and the slot of every sorted pair; the two
-  // kernels touch disjoint tiles
+void launch_ranges(const Layout& L, void* ws, hipStream_t st) {
+  // each tile's list by depth, and the slot of every sorted pair
   const int64_t T = L.total_tiles;
-  hipStream_t lst = st;
-  if (side) {
-    hipError_t e = hipEventRecord(fork, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
-    if (e != hipSuccess) return e;
-    lst = side;
-  }
-  hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)std::min<int64_t>(T, kLongBlocks)), dim3(256),
-                     0, lst, at<const uint4>(ws, L.o_tinfo), T, at<uint32_t>(ws, L.o_vals),
-                     at<const uint32_t>(ws, L.o_pslot), at<const uint32_t>(ws, L.o_pdep),
-                     at<uint32_t>(ws, L.o_spair), at<uint32_t>(ws, L.o_keys2),
-                     at<uint32_t>(ws, L.o_vals2));
-  if (side) {
-    hipError_t e = hipEventRecord(join, side);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_tile_sort_short, dim3((unsigned)std::min<int64_t>(T, kShortBlocks)),
-                     dim3(64), 0, st, at<const uint4>(ws, L.o_tinfo),
-                     at<const uint32_t>(ws, L.o_histtmp), at<uint32_t>(ws, L.o_vals),
-                     at<const uint32_t>(ws, L.o_pslot), at<const uint32_t>(ws, L.o_pdep),
-                     at<uint32_t>(ws, L.o_spair));
-  return side ? hipStreamWaitEvent(st, join, 0) : hipSuccess;
+  // a list of more than kSortRun entries needs that many pairs
+  const bool merge = L.cap > (int64_t)kSortRun;
+  hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)std::min<int64_t>(T, kSortBlocks)), dim3(256), 0,
+                     st, at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_histtmp),
+                     at<uint32_t>(ws, L.o_vals), at<const uint32_t>(ws, L.o_pslot),
+                     at<const uint32_t>(ws, L.o_pdep), at<uint32_t>(ws, L.o_spair),
+                     at<uint32_t>(ws, L.o_keys2), at<uint32_t>(ws, L.o_vals2));
+  if (merge)
+    hipLaunchKernelGGL(k_tile_merge, dim3(1024), dim3(256), 0, st,
+                       at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_histtmp),
+                       at<const uint32_t>(ws, L.o_pslot), at<const uint32_t>(ws, L.o_keys2),
+                       at<const uint32_t>(ws, L.o_vals2), at<uint32_t>(ws, L.o_vals),
+                       at<uint32_t>(ws, L.o_spair));
 }
 
 }  // namespace rogs
