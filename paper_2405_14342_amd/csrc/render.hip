@@ -19,9 +19,9 @@
 // test of each entry against the wave's own pixels (part_reached) leaves out
 // the half or more that reach other parts only.  Measured with 16 x 16 tiles,
 // 4 pixels per lane in one wave -> four waves with the test: 200k surfels x 6
-// views of 1600 x 900, C = 8: forward 563 -> 229 us, backward 666 -> 408 us,
-// fused step 918 -> 496 us; a 640 x 360 colour view of 3M surfels, C = 16:
-// forward 1029 -> 378 us.  One-wave tiles keep the untested walk in the fused
+// views of 1600 x 900, C = 8: forward 563 -> 213 us, backward 666 -> 429 us,
+// fused step 918 -> 515 us; a 640 x 360 colour view of 3M surfels, C = 16:
+// forward 1029 -> 317 us.  One-wave tiles keep the untested walk in the fused
 // step and the backward: there at most 4 % of the entries a wave visits reach
 // none of its pixels, less than the test costs.
 //
@@ -173,8 +173,8 @@ __device__ __forceinline__ uint32_t stage_entries(uint32_t base, int cnt, uint32
 }
 
 // The forward state of a pixel (Eq. 6): acc = sum w f (features, then with kD
-// the relative depth sum w (t_z - t0)), the transmittance T and nl = entries
-// up to the one that stopped the pixel.  With kD, t0 = the depth of the
+// the relative depth sum w (t_z - t0)), the transmittance T and nl = the walked
+// entries up to the one that stopped the pixel.  With kD, t0 = the depth of the
 // pixel's first contributing entry: the list is in ascending depth, so the
 // running minimum of the contributing depths (FLT_MAX while none).
 template <int C>
@@ -195,18 +195,16 @@ __device__ __forceinline__ void pixel_start(const TileGeom& tg, Pixel<C>& p) {
   for (int f = 0; f <= 3 + C; ++f) p.acc[f] = 0.0f;
 }
 
-// One staged list entry for a pixel; returns its footprint weight g.  seen =
-// the entry's position in the tile's list plus one.  ch (ROGS_CH_* bits,
-// uniform): the colour, semantic and depth sums are formed only when
-// selected; T, nl and the order of operations do not depend on it.
+// One staged list entry for a pixel; returns its footprint weight g.  ch
+// (ROGS_CH_* bits, uniform): the colour, semantic and depth sums are formed
+// only when selected; T, nl and the order of operations do not depend on it.
 // Lanes whose pixel the entry does not reach, or has stopped, run the same
 // arithmetic with g = 0: w = 0 leaves T and the sums as they are (T >= 0 and
 // every feature is finite), so the result is that of a branch around the
 // update without its exec-mask bookkeeping.
 template <int C, bool kD>
-__device__ __forceinline__ float entry_forward(const TileGeom& tg, const float4* s, uint32_t seen,
-                                               float qcut, float amax, float teps, uint32_t ch,
-                                               Pixel<C>& p) {
+__device__ __forceinline__ float entry_forward(const TileGeom& tg, const float4* s, float qcut,
+                                               float amax, float teps, uint32_t ch, Pixel<C>& p) {
   // every multiply-add is written out: the forward rounds the same in every
   // kernel it is inlined into
 #pragma clang fp contract(off)
@@ -241,8 +239,9 @@ __device__ __forceinline__ float entry_forward(const TileGeom& tg, const float4*
     p.acc[F] = __builtin_fmaf(w, r1.w - p.t0, p.acc[F]);
   }
   p.T -= w;                     // T (1 - alpha)
-  // at the entry that stops the pixel, its position in the list plus one
-  p.nl = live ? seen : p.nl;
+  // entries walked while live: at the entry that stops the pixel, its place
+  // among the walked ones plus one
+  p.nl += live ? 1u : 0u;
   return g;
 }
 
@@ -276,7 +275,6 @@ __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, flo
   bool stop_all = false;
   for (uint32_t base = tg.rbeg; base < tg.rend && !stop_all; base += KS) {
     const int cnt = (int)min((uint32_t)KS, tg.rend - base);
-    const uint32_t seen0 = base - tg.rbeg + 1u;
     const uint32_t e = stage_entries<FS4, true>(base, cnt, tg.sbase, vals, spair, rec, feat, s_st,
                                                 s_st + 1, s_st + 2);
     if (base == tg.rbeg) e_first = e;
@@ -291,7 +289,7 @@ __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, flo
 #pragma unroll
       for (int j = 0; j < kG; ++j) {
         if (j < cnt && !stop_all) {
-          gsave[j] = entry_forward<C, false>(tg, s_st + j * ES, seen0 + j, qcut, amax, teps, ch, p);
+          gsave[j] = entry_forward<C, false>(tg, s_st + j * ES, qcut, amax, teps, ch, p);
           if (j % kFwdUnroll == kFwdUnroll - 1 && all_stopped<C>(p, teps)) stop_all = true;
         } else {
           gsave[j] = 0.0f;
@@ -304,7 +302,7 @@ __device__ __forceinline__ void forward_tile(const TileGeom& tg, float qcut, flo
       for (int u = 0; u < kFwdUnroll; ++u) {
         const int j = j0 + u;
         if (j >= cnt) break;
-        (void)entry_forward<C, false>(tg, s_st + j * ES, seen0 + j, qcut, amax, teps, ch, p);
+        (void)entry_forward<C, false>(tg, s_st + j * ES, qcut, amax, teps, ch, p);
       }
       if (all_stopped<C>(p, teps)) stop_all = true;
     }
@@ -323,7 +321,7 @@ __device__ __forceinline__ void forward_part(const TileGeom& tg, float qcut, flo
                                              float teps, const uint32_t* __restrict__ spair,
                                              const float4* __restrict__ rec,
                                              const float4* __restrict__ feat, float4* s_st,
-                                             Pixel<C>& p, uint32_t ch) {
+                                             uint32_t* s_pos, Pixel<C>& p, uint32_t ch) {
   constexpr int FS4 = (3 + C + 4) / 4;
   constexpr int ES = 2 + FS4;
   const int lane = threadIdx.x & 63;
@@ -341,7 +339,7 @@ __device__ __forceinline__ void forward_part(const TileGeom& tg, float qcut, flo
   for (uint32_t base = 0; base < len; base += 64u) {
     r1.y *= 2.0f;                                        // A, 2B, C, t_z
     const bool in = base + lane < len && part_reached(tg, r0, r1, qcut);
-    unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
     const int n = (int)__popcll(m);
     if (in) {
       const int j = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -352,6 +350,7 @@ __device__ __forceinline__ void forward_part(const TileGeom& tg, float qcut, flo
       s[1] = r1;
 #pragma unroll
       for (int f = 0; f < FS4; ++f) s[2 + f] = fr[f];
+      s_pos[j] = base + (uint32_t)lane + 1u;
     }
     slot = slot1;
     if (base + 64u + lane < len) {
@@ -361,17 +360,20 @@ __device__ __forceinline__ void forward_part(const TileGeom& tg, float qcut, flo
     if (base + 128u + lane < len) slot1 = spair[tg.rbeg + base + 128u + lane];
     wave_lds_sync();
     bool stop = false;
+    const bool was_live = p.T >= teps;
+    const uint32_t nl = p.nl;
+    p.nl = 0;
     for (int j0 = 0; j0 < n && !stop; j0 += kFwdUnroll) {
 #pragma unroll
       for (int u = 0; u < kFwdUnroll; ++u) {
         const int j = j0 + u;
         if (j >= n) break;
-        const uint32_t seen = base + (uint32_t)__builtin_ctzll(m) + 1u;
-        m &= m - 1ull;
-        (void)entry_forward<C, kD>(tg, s_st + j * ES, seen, qcut, amax, teps, ch, p);
+        (void)entry_forward<C, kD>(tg, s_st + j * ES, qcut, amax, teps, ch, p);
       }
       stop = all_stopped<C>(p, teps);
     }
+    // a pixel that stopped here: its stopping entry's place in the tile's list
+    p.nl = was_live && p.T < teps ? s_pos[p.nl - 1u] : nl;
     wave_lds_sync();
     if (stop) break;
   }
@@ -391,19 +393,16 @@ static_assert(kWFloats >= 64 * 17, "transpose space");
 template <int C>
 constexpr int kNFB() { return (3 + C + 1 + 15) / 16; }
 
-// Feature and depth gradients of up to 16 list entries as one matrix product
-// on the matrix cores: D[m][n] = sum over the wave's pixels p of
-// w[m][p] * gamma[p][n], where gamma[p] = (dL/dfeatures, dL/dD) of pixel p.
+// Feature and depth gradients of 16 list entries as one matrix product on the
+// matrix cores: D[m][n] = sum over the wave's pixels p of w[m][p] *
+// gamma[p][n], where gamma[p] = (dL/dfeatures, dL/dD) of pixel p.
 // v_mfma_f32_16x16x4_f32 takes A[m][k] from lane m + 16k, B[k][n] from lane
 // n + 16k and returns D[4g + i][n] in lane n + 16g, element i.  The k-th
 // step of 4 covers pixels kgrp * 16 + c, so a lane reads its A operands as 16
-// contiguous floats of its entry's row.  Row m goes to record s_e[m] of dst.
+// contiguous floats of its entry's row.
 template <int C>
-__device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s_e, int nrows,
-                                             const float (&bG)[kNFB<C>()][16], float* dst) {
-  constexpr int F = 3 + C;
-  constexpr uint32_t GS = grad_stride_c(C);
-  constexpr int NG = F + 1;
+__device__ __forceinline__ void feature_product(const float* s_w, const float (&bG)[kNFB<C>()][16],
+                                                mfma_f4 (&acc)[kNFB<C>()]) {
   const int lane = threadIdx.x & 63;
   const int mrow = lane & 15, kgrp = lane >> 4;
   float a[16];
@@ -413,6 +412,24 @@ __device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s
     const float4 t = ap[q];
     a[4 * q] = t.x; a[4 * q + 1] = t.y; a[4 * q + 2] = t.z; a[4 * q + 3] = t.w;
   }
+#pragma unroll
+  for (int nb = 0; nb < kNFB<C>(); ++nb) {
+    acc[nb] = mfma_f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], bG[nb][c], acc[nb], 0, 0, 0);
+  }
+}
+
+// The products of a one-wave tile's entries, row m < nrows to its record s_e[m].
+template <int C>
+__device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s_e, int nrows,
+                                             const float (&bG)[kNFB<C>()][16],
+                                             float* __restrict__ gpair) {
+  constexpr int F = 3 + C;
+  constexpr uint32_t GS = grad_stride_c(C);
+  const int lane = threadIdx.x & 63;
+  const int mrow = lane & 15, kgrp = lane >> 4;
   uint32_t e4[4];
   bool ok[4];
 #pragma unroll
@@ -421,20 +438,34 @@ __device__ __forceinline__ void feature_gemm(const float* s_w, const uint32_t* s
     ok[i] = m < nrows;
     e4[i] = s_e[m];
   }
+  mfma_f4 acc[kNFB<C>()];
+  feature_product<C>(s_w, bG, acc);
 #pragma unroll
   for (int nb = 0; nb < kNFB<C>(); ++nb) {
-    mfma_f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], bG[nb][c], acc, 0, 0, 0);
     const int n = nb * 16 + mrow;
-    if (n < NG) {
+    if (n <= F) {
       const int col = n < F ? 7 + n : 6;       // record: ..., dt_z (6), features (7 ...)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (ok[i]) dst[(size_t)e4[i] * GS + col] = acc[i];
+        if (ok[i]) gpair[(size_t)e4[i] * GS + col] = acc[nb][i];
     }
   }
+}
+
+// A part's share of 16 entries' products, row m at s_w[m NF] over the weight
+// rows that were read.
+template <int C>
+__device__ __forceinline__ void feature_share(float* s_w, const float (&bG)[kNFB<C>()][16]) {
+  constexpr int NF = 16 * kNFB<C>();
+  const int lane = threadIdx.x & 63;
+  const int mrow = lane & 15, kgrp = lane >> 4;
+  mfma_f4 acc[kNFB<C>()];
+  feature_product<C>(s_w, bG, acc);
+  wave_lds_sync();
+#pragma unroll
+  for (int nb = 0; nb < kNFB<C>(); ++nb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_w[(4 * kgrp + i) * NF + nb * 16 + mrow] = acc[nb][i];
 }
 
 // A pixel's inputs of the backward: the output gradient Gv (features, depth,
@@ -486,22 +517,18 @@ __device__ __forceinline__ void transpose_grad(const PixelGrad<C>& pg, float* s_
   }
 }
 
-constexpr int kReduced = 6;     // gradient values per entry summed across the wave
+constexpr int kReduced = 6;     // gradient values per entry summed across the tile
 
 // One staged list entry of the backward for a pixel with footprint weight g
-// (0 where the entry does not reach it): its weight w and pv = the five
-// moments of gda and dalpha.
-//   per pair: sum gda dx, sum gda dy, sum gda dx^2, sum gda dx dy,
-//   sum gda dy^2 (gda = dL/d(alpha) per pixel; dL/dq = -(alpha / 2) gda),
-//   dalpha = sum gda, dtz, drgb[3], dsem[C]
+// (0 where the entry does not reach it): its weight w and gda = g dL/d(alpha
+// g) = alpha dL/d(alpha), so that dL/dq = -(alpha / 2) gda.
 // Lanes whose pixel the pair does not reach run the same arithmetic with
 // g = 0: alpha = w = 0, T and the prefix unchanged, terms +-0 (a pair that
 // reaches no pixel of the wave gets a zero record this way; a branch around
 // it would copy T and the prefix on every entry).
 template <int C, bool kDA>
-__device__ __forceinline__ float entry_backward(const float* fv, float tz, float dx, float dy,
-                                                float g, float amax, const PixelGrad<C>& pg,
-                                                PixelBack& b, float (&pv)[kReduced]) {
+__device__ __forceinline__ float entry_backward(const float* fv, float tz, float g, float amax,
+                                                const PixelGrad<C>& pg, PixelBack& b, float& gda) {
   // every multiply-add is written out: the backward rounds the same in the
   // fused step and in the stand-alone backward
 #pragma clang fp contract(off)
@@ -523,18 +550,23 @@ __device__ __forceinline__ float entry_backward(const float* fv, float tz, float
   // where it does not hold (0 where it does), and dL/dq = -(alpha / 2)
   // gda, the factor -alpha / 2 being applied to the slot's sums by
   // the projection adjoint
-  const float gda = araw > amax ? 0.0f : g * da;
-  // moments of gda over the pixel offsets; the projection adjoint
-  // turns them into dL/d(u, v, A, B, C) with the pair's conic
-  const float gx = gda * dx, gy = gda * dy;
-  pv[5] = gda;
-  pv[0] = gx;
-  pv[1] = gy;
-  pv[2] = gx * dx;
-  pv[3] = gx * dy;
-  pv[4] = gy * dy;
+  gda = araw > amax ? 0.0f : g * da;
   b.T -= w;                       // as in the forward
   return w;
+}
+
+// Adds a pixel's moments of gda over the pixel offsets and gda itself (pv = 0
+// before the first: fma(x, y, 0) rounds as x y); the projection adjoint turns
+// a slot's sums into dL/d(u, v, A, B, C) with the pair's conic.
+__device__ __forceinline__ void add_moments(float gda, float dx, float dy, float (&pv)[kReduced]) {
+#pragma clang fp contract(off)
+  const float gx = gda * dx, gy = gda * dy;
+  pv[5] += gda;
+  pv[0] += gx;
+  pv[1] += gy;
+  pv[2] = __builtin_fmaf(gx, dx, pv[2]);
+  pv[3] = __builtin_fmaf(gx, dy, pv[3]);
+  pv[4] = __builtin_fmaf(gy, dy, pv[4]);
 }
 
 template <int FS4>
@@ -617,9 +649,10 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
         }
         float fv[FS4 * 4];
         load_features<FS4>(s, fv);
-        float pv[NR];
-        s_w[(j - j0) * kWRow + lane] =
-            entry_backward<C, kDA>(fv, r1.w, dx, dy, g, amax, pg, b, pv);
+        float gda;
+        s_w[(j - j0) * kWRow + lane] = entry_backward<C, kDA>(fv, r1.w, g, amax, pg, b, gda);
+        const float gx = gda * dx, gy = gda * dy;
+        const float pv[NR] = {gx, gy, gx * dx, gx * dy, gy * dy, gda};
         const float tot = wave_reduce_scatter<NR>(pv, lane);
         if (kPadCol || writer) gcol[(size_t)e * GS] = tot;
       };
@@ -648,25 +681,30 @@ __device__ __forceinline__ void backward_tile(const TileGeom& tg, float qcut, fl
   }
 }
 
-// LDS of a tile of NW waves (parts) in the backward: the staged entries, the
-// waves' weight rows and partial records, and per wave which staged entries it
-// took part in and the rows of its present block of 16.
+// LDS of a tile of NW waves (parts) in the backward: the staged entries; per
+// wave the weight rows of a block of 16 entries, then its share of their
+// feature gradients; the gda of all the tile's pixels for the block; per wave
+// which staged entries reach it.  A one-wave tile has its weight rows only.
 template <int C, int NW, int KS>
 struct alignas(16) BlockLds {
   float4 st[KS * (2 + (3 + C + 4) / 4)];
   float w[NW][kWFloats];
-  float part[NW][NW == 1 ? 4 : KS * grad_stride_c(C)];    // one wave writes its records directly
+  float g[NW == 1 ? 4 : 16 * 64 * NW];
   unsigned long long mask[NW];
-  uint32_t row[NW][16];
   uint32_t e[KS];
   uint32_t maxn[NW];
 };
 
-// Backward pass of a tile of NW waves.  The block stages KS list entries; each
-// wave tests them against its own part (lane j tests entry j), walks the ones
-// that reach it in blocks of 16 and leaves its partial record of each in LDS;
-// then the block adds the waves' partials in wave order and writes each pair's
-// record whole.  A wave whose part an entry does not reach adds nothing.
+// Backward pass of a tile of NW waves, in blocks of 16 list entries and two
+// phases.  First every wave walks the entries for its own pixels, leaving out
+// those that do not reach its part (lane j has tested entry j): it leaves each
+// pixel's gda in LDS and forms its part's share of the feature gradients on
+// the matrix cores.  Then the waves share the block's records: each takes
+// 16 / NW entries and reduces their moments, over the parts first, per lane,
+// then across the lanes (the order of one wave with NW pixels per lane), and
+// the features' shares are added in part order.  So the reduce-scatter runs
+// once per entry, not once per part, and a part that an entry does not reach
+// costs nothing.
 template <int C, int NW, int KS, bool kDA>
 __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, float amax,
                                                const uint32_t* __restrict__ vals,
@@ -675,22 +713,23 @@ __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, f
                                                const float4* __restrict__ feat,
                                                BlockLds<C, NW, KS>& L, const PixelGrad<C>& pg,
                                                float* __restrict__ gpair) {
+#pragma clang fp contract(off)
   constexpr int F = 3 + C;
   constexpr int FS4 = (F + 4) / 4;
   constexpr int ES = 2 + FS4;
   constexpr int NV = 10 + C;
   constexpr uint32_t GS = grad_stride_c(C);
-  constexpr int Q = (int)GS / 4;
   constexpr int NR = kReduced;
   constexpr int NT = 64 * NW;
+  constexpr int NF = 16 * kNFB<C>();                 // columns of a share of the features
+  static_assert(16 * NF <= kWFloats, "feature shares over the weight rows");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* const s_w = L.w[wv];
-  float* const s_p = L.part[wv];
   const int my_comp = rs_comp(lane, NR);
   constexpr bool kPadCol = GS > (uint32_t)NV;
   const bool writer = kPadCol || (my_comp >= 0 && (lane & rs_dup_bits(NR)) == 0);
-  float* const pcol = s_p + (my_comp >= 0 ? my_comp : (kPadCol ? NV : 0));
+  float* const gcol = gpair + (my_comp >= 0 ? my_comp : (kPadCol ? NV : 0));
+  float* const s_w = L.w[wv];
   PixelBack b = back_start<C, kDA>(pg);
   const uint32_t my_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(pg.nl));
   if (lane == 0) L.maxn[wv] = my_max;
@@ -698,9 +737,13 @@ __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, f
   uint32_t maxn = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) maxn = max(maxn, L.maxn[w]);
-  const uint32_t stop = tg.rbeg + min(maxn, tg.rend - tg.rbeg);
+  const uint32_t stop =
+      tg.rbeg + min((uint32_t)__builtin_amdgcn_readfirstlane((int)maxn), tg.rend - tg.rbeg);
   float bG[kNFB<C>()][16];
   if (my_max > 0u) transpose_grad<C>(pg, s_w, bG);
+  // rows between a lane's pixels of two parts
+  const float drow = (float)(64 >> __builtin_ctz((unsigned)tg.vw->tw));
+  const float py0 = tg.pyc - (float)tg.part * drow;      // exact: halves below 2^15
   for (uint32_t base = tg.rbeg; base < stop; base += KS) {
     const int cnt = (int)min((uint32_t)KS, stop - base);
     if (tid < cnt) L.e[tid] = vals[base + tid];
@@ -717,14 +760,14 @@ __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, f
     const bool in = lane < cnt && seen + (uint32_t)lane < my_max &&
                     part_reached(tg, L.st[min(lane, KS - 1) * ES], L.st[min(lane, KS - 1) * ES + 1],
                                  qcut);
-    unsigned long long m = __builtin_amdgcn_ballot_w64(in);
-    if (lane == 0) L.mask[wv] = m;
-    while (m) {
-      int n = 0;
-      for (; n < 16 && m; ++n) {
-#pragma clang fp contract(off)
-        const int j = __builtin_ctzll(m);
-        m &= m - 1ull;
+    const unsigned long long mine = __builtin_amdgcn_ballot_w64(in);
+    if (lane == 0) L.mask[wv] = mine;
+    for (int j0 = 0; j0 < cnt; j0 += 16) {
+      const int n = min(16, cnt - j0);
+      const uint32_t m16 = (uint32_t)(mine >> j0) & 0xffffu;
+      for (uint32_t m = m16; m; m &= m - 1u) {
+        const int i = __builtin_ctz(m);
+        const int j = j0 + i;
         const float4* s = L.st + j * ES;
         const float4 r0 = s[0], r1 = s[1];
         const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
@@ -734,35 +777,50 @@ __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, f
         const float g = (seen + (uint32_t)j < pg.nl && q <= qcut) ? ge : 0.0f;
         float fv[FS4 * 4];
         load_features<FS4>(s, fv);
-        float pv[NR];
-        s_w[n * kWRow + lane] = entry_backward<C, kDA>(fv, r1.w, dx, dy, g, amax, pg, b, pv);
-        const float tot = wave_reduce_scatter<NR>(pv, lane);
-        if (writer) pcol[j * GS] = tot;
-        if (lane == 0) L.row[wv][n] = (uint32_t)j;
+        float gda;
+        s_w[i * kWRow + lane] = entry_backward<C, kDA>(fv, r1.w, g, amax, pg, b, gda);
+        L.g[i * NT + tid] = gda;
       }
-      wave_lds_sync();
-      feature_gemm<C>(s_w, L.row[wv], n, bG, s_p);
-      wave_lds_sync();
-    }
-    __syncthreads();
-    for (int t = tid; t < cnt * Q; t += NT) {
-      const int j = t / Q;
-      float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (m16) {
+        wave_lds_sync();
+        // (rows of entries that do not reach the part hold leftovers: their
+        // results are not read)
+        feature_share<C>(s_w, bG);
+      }
+      __syncthreads();
+      // the parts that each entry reaches
+      uint32_t part16[NW];
 #pragma unroll
       for (int w = 0; w < NW; ++w)
-        if ((L.mask[w] >> j) & 1ull) {
-          const float4 y = reinterpret_cast<const float4*>(L.part[w])[t];
-          x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+        part16[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(L.mask[w] >> j0)) &
+                    0xffffu;
+      for (int i = wv; i < n; i += NW) {
+        const float4 r0 = L.st[(j0 + i) * ES];
+        const float dx = pixel_offset(tg.pxc, r0.x, r0.z);
+        float pv[NR] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        float fs = 0.0f;                                 // lane = feature column
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          if (!((part16[w] >> i) & 1u)) continue;
+          add_moments(L.g[i * NT + 64 * w + lane], dx,
+                      pixel_offset(py0 + (float)w * drow, r0.y, r0.w), pv);
+          if (lane <= F) fs += L.w[w][i * NF + lane];
         }
-      reinterpret_cast<float4*>(gpair)[(size_t)L.e[j] * Q + (t - j * Q)] = x;
+        const size_t e = (size_t)L.e[j0 + i] * GS;
+        const float tot = wave_reduce_scatter<NR>(pv, lane);
+        if (writer) gcol[e] = tot;
+        // record: ..., dt_z (6), features (7 ...)
+        if (lane <= F) gpair[e + (lane < F ? 7 + lane : 6)] = fs;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   // pairs that no pixel of the tile reached contribute nothing
-  const uint32_t nz = (tg.rend - stop) * (uint32_t)Q;
+  constexpr uint32_t Q = GS / 4;
+  const uint32_t nz = (tg.rend - stop) * Q;
   for (uint32_t t = (uint32_t)tid; t < nz; t += NT) {
-    const uint32_t j = t / (uint32_t)Q;
-    reinterpret_cast<float4*>(gpair)[(size_t)vals[stop + j] * Q + (t - j * (uint32_t)Q)] =
+    const uint32_t j = t / Q;
+    reinterpret_cast<float4*>(gpair)[(size_t)vals[stop + j] * Q + (t - j * Q)] =
         make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
 }
@@ -784,12 +842,14 @@ __global__ __launch_bounds__(64 * NW) void k_render_fwd(
   constexpr int NO = 5 + C;           // output channels
   // staged entries: projection record, conic, features, one record per entry
   __shared__ float4 s_st[NW][64 * (2 + FS4)];
+  __shared__ uint32_t s_pos[NW][64];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const TileGeom tg = tile_geom(views, N, tinfo, wv);
   const uint32_t ch = (uint32_t)tg.vw->ch & mask;
   constexpr uint32_t kPlanes = ROGS_CH_RGB | ROGS_CH_SEM | ROGS_CH_D | ROGS_CH_A;
   Pixel<C> p;
-  forward_part<C, true>(tg, qcut, amax, teps, spair, rec, feat, s_st[wv], p, ch);
+  forward_part<C, true>(tg, qcut, amax, teps, spair, rec, feat, s_st[wv], s_pos[wv], p,
+                        ch);
   if (!(tg.px < tg.W && tg.py < tg.H)) return;
   const uint32_t len = tg.rend - tg.rbeg;
   const size_t HW = (size_t)tg.W * tg.H;
@@ -907,13 +967,13 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, NW, KS>()))) void k_render_ste
     FusedLoss fl) {
   constexpr int F = 3 + C;
   constexpr int FS4 = (F + 4) / 4;
-  // the forward of several waves stages in regions of their own, over the
-  // space of the waves' weight rows and partial records
+  // the forward of several waves stages in regions of their own
   union Lds {
     BlockLds<C, NW, KS> b;
     float4 f[NW == 1 ? 1 : NW][NW == 1 ? 1 : 64 * (2 + FS4)];
   };
   __shared__ Lds L;
+  __shared__ uint32_t s_pos[NW == 1 ? 1 : NW][NW == 1 ? 1 : 64];
   __shared__ float s_l[3 * NW];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const TileGeom tg = tile_geom(views, N, tinfo, NW == 1 ? 0 : wv);
@@ -961,7 +1021,8 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerEu<C, NW, KS>()))) void k_render_ste
     forward_tile<C, KS, kG>(tg, qcut, amax, teps, vals, spair, rec, feat, L.b.st, px, e_first, kCh,
                             gsv);
   else
-    forward_part<C, false>(tg, qcut, amax, teps, spair, rec, feat, L.f[wv], px, kCh);
+    forward_part<C, false>(tg, qcut, amax, teps, spair, rec, feat, L.f[wv], s_pos[wv], px,
+                           kCh);
   // loss epilogue: dL/dO and G.O per pixel, this tile's loss partials
   const uint32_t len = tg.rend - tg.rbeg;
   float l = 0.0f, dal = 0.0f, dbl = 0.0f;
