@@ -505,7 +505,8 @@ int rogs_project(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, in
   r = upload_views(c, L, cams, ws, st);
   if (r != ROGS_OK) return r;
   prof_begin(c, 0, st);
-  rogs::launch_project(L, ws, s, true, st);
+  rogs::launch_project(L, ws, s, st);
+  rogs::launch_pack_feat(L, ws, s, st);
   prof_end(c, st);
   prof_begin(c, 1, st);
   rogs::launch_scan_part(L, ws, st);
@@ -856,13 +857,13 @@ int fused_sequence(rogs_ctx* c, Layout& L, const rogs_train_state* t, const rogs
   rogs_surfels s = fused_surfels(t);
   prof_begin(c, 0, st);
   // the same launch counts the loss mask per view and clears the tile counters
-  rogs::launch_project(L, ws, &s, true, st, tg->mask);
+  rogs::launch_project(L, ws, &s, st, tg->mask);
   prof_end(c, st);
   prof_begin(c, 1, st);
   rogs::launch_scan_part(L, ws, st, true);
   prof_end(c, st);
   prof_begin(c, 3, st);
-  rogs::launch_binning(L, ws, -1, -1, st, true);
+  rogs::launch_binning(L, ws, -1, -1, st, &s);
   prof_end(c, st);
   prof_begin(c, 4, st);
   rogs::launch_ranges(L, ws, st);

@@ -49,7 +49,8 @@ struct ViewDev {
 
 // Number of semantic classes with a compiled kernel set.
 inline bool sem_supported(int C) { return (C >= 1 && C <= 8) || C == 16; }
-inline int feat_stride(int C) { return ((4 + C) + 3) & ~3; }      // rgb, sem, alpha; float4-padded
+// rgb, sem, alpha; float4-padded: 8, 12 or 20
+inline int feat_stride(int C) { return ((4 + C) + 3) & ~3; }
 // floats per per-pair gradient record: 10 + C values padded to whole float4
 __host__ __device__ constexpr uint32_t grad_stride_c(int C) { return ((10 + C) + 3) & ~3; }
 inline int grad_stride(int C) { return (int)grad_stride_c(C); }
@@ -389,6 +390,52 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* s_w, u
   return pre + inc - x;
 }
 
+// Feature records feat[N][4 Q] (rgb, sem[C], alpha, zero padding) of the
+// surfels of one range of kProjBlock, from the surfel SoA, by a block of
+// kProjBlock threads: Q float4 of the output per thread, consecutive threads
+// storing consecutive ones; the four values of a float4 are read from four
+// rows, all of a thread's loads before its stores (one memory round trip).
+template <int Q>
+__device__ __forceinline__ void pack_features_q(int range, int N, int C,
+                                                const float* __restrict__ pa,
+                                                const float* __restrict__ prgb,
+                                                const float* __restrict__ psem,
+                                                float4* __restrict__ feat) {
+  const int first = range * kProjBlock;
+  const int n4 = min(kProjBlock, N - first) * Q;
+  float v[Q][4];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    const int t = threadIdx.x + u * kProjBlock;
+    const int j = t / Q, q = t - j * Q;
+    const size_t i = (size_t)first + j;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int r = 4 * q + k;      // record column: rgb 0-2, sem 3..3+C-1, alpha 3+C
+      v[u][k] = t >= n4 || r > 3 + C ? 0.0f
+                : r < 3              ? prgb[(size_t)r * N + i]
+                : r < 3 + C          ? psem[(size_t)(r - 3) * N + i]
+                                     : pa[i];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    const int t = threadIdx.x + u * kProjBlock;
+    if (t < n4) feat[(size_t)first * Q + t] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+  }
+}
+
+__device__ __forceinline__ void pack_features(int range, int N, int C, int FS,
+                                              const float* __restrict__ pa,
+                                              const float* __restrict__ prgb,
+                                              const float* __restrict__ psem,
+                                              float4* __restrict__ feat) {
+  // the strides of 1-4, 5-8 and 16 classes (feat_stride)
+  if (FS == 8) pack_features_q<2>(range, N, C, pa, prgb, psem, feat);
+  else if (FS == 12) pack_features_q<3>(range, N, C, pa, prgb, psem, feat);
+  else pack_features_q<5>(range, N, C, pa, prgb, psem, feat);
+}
+
 // Last index j in [0, n) with off[j] <= k, for non-decreasing off with off[0] <= k.
 __device__ __forceinline__ int last_le(const uint32_t* off, int n, uint32_t k) {
   int lo = 0, hi = n - 1;
@@ -644,16 +691,20 @@ struct AdamArgs {
 
 // ------------------------------------------------------------------ launchers
 
-void launch_project(const Layout& L, void* ws, const rogs_surfels* s, bool pack_feat,
-                    hipStream_t st, const uint8_t* mask = nullptr);
+void launch_project(const Layout& L, void* ws, const rogs_surfels* s, hipStream_t st,
+                    const uint8_t* mask = nullptr);
+// Feature records of the surfels that some view sees; after launch_project and
+// before launch_scan_part.
+void launch_pack_feat(const Layout& L, void* ws, const rogs_surfels* s, hipStream_t st);
 void launch_scan_part(const Layout& L, void* ws, hipStream_t st, bool mask_parts = false);
 // Compaction of the visible slots, emission with per-tile counting, the
 // tiles' first list positions, ranges and compositing work items, and the
 // pairs grouped by tile (o_vals).  Counts
-// < 0 are read on the device.  counts_cleared: the per-tile counters were
-// zeroed by the projection launch.
+// < 0 are read on the device.  fused: the per-tile counters were zeroed by the
+// projection launch, and the compaction packs the feature records of s
+// (nullptr otherwise).
 void launch_binning(const Layout& L, void* ws, int64_t n_pairs, int64_t n_vis, hipStream_t st,
-                    bool counts_cleared = false);
+                    const rogs_surfels* fused = nullptr);
 // Each tile's list by depth.
 void launch_ranges(const Layout& L, void* ws, hipStream_t st);
 void launch_count_work(const Layout& L, void* ws, unsigned long long* counts, hipStream_t st);

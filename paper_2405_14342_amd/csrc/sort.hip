@@ -27,7 +27,9 @@ constexpr int kEmitWin = 2 * kEmitRows;   // tiles of a block's count window
 // scan of the counts), and the first slot of every emission block of
 // kEmitPairs pairs (each block start lies in exactly one slot; only the nblk
 // launched blocks).  Block 0 also sets the overflow flag from the totals of
-// the count scans (the fused step's scan launch leaves it to this one).
+// the count scans (the fused step's scan launch leaves it to this one).  With
+// feat (the fused step) nb more blocks pack the feature records of the ranges
+// that some view sees, beside the compaction and without a launch of their own.
 __global__ __launch_bounds__(kProjBlock) void k_compact(int V, int N, int nb,
                                                         const uint32_t* __restrict__ cnt,
                                                         const uint32_t* __restrict__ part,
@@ -39,17 +41,31 @@ __global__ __launch_bounds__(kProjBlock) void k_compact(int V, int N, int nb,
                                                         uint32_t* __restrict__ spos,
                                                         uint32_t* __restrict__ bstart,
                                                         uint32_t nblk, uint32_t* __restrict__ misc,
-                                                        int64_t cap) {
+                                                        int64_t cap, int C, int FS,
+                                                        const float* __restrict__ pa,
+                                                        const float* __restrict__ prgb,
+                                                        const float* __restrict__ psem,
+                                                        float4* __restrict__ feat) {
   __shared__ uint32_t s_w[kProjBlock / 64];
   __shared__ uint32_t s_p[kProjBlock / 64];
   if (blockIdx.x == 0 && threadIdx.x == 0)
     misc[kMiscOverflow] =
         ((int64_t)misc[kMiscPairs] > cap || (int64_t)misc[kMiscVisible] > scap) ? 1u : 0u;
+  const size_t nparts = (size_t)V * nb;
+  if (blockIdx.x >= (unsigned)nb) {
+    const int range = (int)blockIdx.x - nb;
+    bool seen = false;
+    for (int v = threadIdx.x; v < V; v += kProjBlock) {
+      const size_t pb = (size_t)v * nb + range;
+      seen = seen || (pb + 1 < nparts ? partv[pb + 1] : misc[kMiscVisible]) != partv[pb];
+    }
+    if (__syncthreads_or(seen)) pack_features(range, N, C, FS, pa, prgb, psem, feat);
+    return;
+  }
   const int i = blockIdx.x * kProjBlock + threadIdx.x;
   const bool valid = i < N;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const size_t nparts = (size_t)V * nb;
   for (int v = 0; v < V; ++v) {
     const size_t slot = (size_t)v * N + i;
     // the scanned visible counts give this block's count in view v: none
@@ -904,7 +920,7 @@ __global__ __launch_bounds__(256) void k_tile_layout(const uint32_t* __restrict_
 // Binning of the current batch.  n_pairs / n_vis >= 0: counts known on the
 // host (exact grids); < 0: read on the device (grids sized by the capacity).
 void launch_binning(const Layout& L, void* ws, int64_t n_pairs, int64_t n_vis, hipStream_t st,
-                    bool counts_cleared) {
+                    const rogs_surfels* fused) {
   uint32_t* misc = at<uint32_t>(ws, L.o_misc);
   const uint32_t* p_dev = n_pairs < 0 ? misc + kMiscPairs : nullptr;
   const uint32_t* s_dev = n_vis < 0 ? misc + kMiscVisible : nullptr;
@@ -913,18 +929,20 @@ void launch_binning(const Layout& L, void* ws, int64_t n_pairs, int64_t n_vis, h
   const int64_t T = L.total_tiles;
   uint32_t* tcnt = at<uint32_t>(ws, L.o_tcnt);
   uint32_t* tstart = at<uint32_t>(ws, L.o_tstart);
-  if (!counts_cleared) fill_u32(tcnt, 0u, T, st);
+  if (!fused) fill_u32(tcnt, 0u, T, st);
   // 1. visible slots in (view, surfel id) order, with their emission counts
   uint32_t* sv = at<uint32_t>(ws, L.o_sval);
   uint32_t* scnt = at<uint32_t>(ws, L.o_scnt);
   uint32_t* soff = at<uint32_t>(ws, L.o_soff);
   //    and first pairs, and the first slot of every emission block
   const uint32_t nblk_emit = (uint32_t)((p_grid + kEmitPairs - 1) / kEmitPairs);
-  hipLaunchKernelGGL(k_compact, dim3(L.nb), dim3(kProjBlock), 0, st, L.V, L.N, L.nb,
+  hipLaunchKernelGGL(k_compact, dim3(fused ? 2 * L.nb : L.nb), dim3(kProjBlock), 0, st, L.V, L.N, L.nb,
                      at<const uint32_t>(ws, L.o_cnt), at<const uint32_t>(ws, L.o_part),
                      at<const uint32_t>(ws, L.o_partv), L.scap, sv, scnt, soff,
                      at<uint32_t>(ws, L.o_pos), at<uint32_t>(ws, L.o_bstart), nblk_emit, misc,
-                     L.cap);
+                     L.cap, L.C, L.FS, fused ? fused->alpha : nullptr,
+                     fused ? fused->rgb : nullptr, fused ? fused->sem : nullptr,
+                     fused ? at<float4>(ws, L.o_feat) : nullptr);
   uint32_t* n_emit = p_dev ? misc + kMiscEmit : nullptr;
   // 2. one (tile, rank) per covered tile, counted per tile
   uint32_t* keys = at<uint32_t>(ws, L.o_keys);
