@@ -396,7 +396,7 @@ ROGS_API int rogs_elev_loss_static(rogs_ctx* ctx, int32_t n, const float* z, con
  * the lower point index: the brute-force result), idx[i] its index
  * (nullable).  The points are bucketed into a uniform grid of about 2m cells
  * over the bounding box of surfels and points, and each surfel searches
- * rings of cells outward until no unvisited cell can hold a nearer point:
+ * cells with points, row by row outward, until none left can hold a nearer point:
  * O(n + m) work for points spread like road returns.  Device arrays; 1 <= m <=
  * 2^29.  scratch: caller-owned device memory, 256-byte aligned, of
  * rogs_lidar_scratch_bytes(n, m) bytes (the grid, the points in cell order). */
