@@ -303,6 +303,15 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
     d.ith = 1.0 / (double)vth;
     d.tiles_x = (k.w + vtw - 1) / vtw;
     d.tiles_y = (k.h + vth - 1) / vth;
+    double rn[3];
+    for (int j = 0; j < 3; ++j)
+      rn[j] = sqrt((double)k.R_cw[3 * j] * k.R_cw[3 * j] + (double)k.R_cw[3 * j + 1] * k.R_cw[3 * j + 1] +
+                   (double)k.R_cw[3 * j + 2] * k.R_cw[3 * j + 2]);
+    const bool pin = k.model == ROGS_PINHOLE;
+    d.kx = 1.000001 * (double)k.fx * (rn[0] + (pin ? d.limx * rn[2] : 0.0));
+    d.ky = 1.000001 * (double)k.fy * (rn[1] + (pin ? d.limy * rn[2] : 0.0));
+    d.wpad = (double)d.tiles_x * vtw;
+    d.hpad = (double)d.tiles_y * vth;
     d.tile_off = (int32_t)tiles;
     d.ch = ch ? ch[v] : (uint32_t)ROGS_CH_ALL;
     vt[v] = d;

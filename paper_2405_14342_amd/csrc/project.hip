@@ -5,27 +5,37 @@
 // into one view (the other views' blocks of a surfel range find its
 // parameters in the cache); per-view results land in "slot" arrays indexed
 // v * N + i.
+#include <math.h>
+
+#include <algorithm>
+
 #include "rogs_internal.h"
 
 namespace rogs {
 
 namespace {
 
+// (range, view) pairs from which a list pays: its launch costs about 10 us and a
+// culled block of the direct launch 1.2 ns.  Listed against direct: 70000 pairs
+// (6 views of 3M surfels) 73 / 95 us, 75000 (24 of 800k, fewer of them culled)
+// 204 / 209, 11700 (one view of 3M) 22 / 19, 4700 (an export's chunk) 41 / 24.
+constexpr int64_t kProjListMin = 32768;
+constexpr int64_t kProjListBlocks = 6144;   // blocks that stride over it
+
 __device__ __forceinline__ uint32_t nonzero_bytes4(uint32_t x) {
   return ((x & 0xffu) != 0u) + ((x & 0xff00u) != 0u) + ((x & 0xff0000u) != 0u) +
          ((x & 0xff000000u) != 0u);
 }
 
-// Extra blocks of the fused step's projection launch, block (nb + c, v):
-// the nonzero bytes of chunk c (kMaskChunk bytes) of view v's loss mask into
+// Extra blocks of the fused step's projection launch, chunk c of view v: the
+// nonzero bytes of chunk c (kMaskChunk bytes) of view v's loss mask into
 // mpart[v * nmb + c] (summed per view by the count-table scan), and a share
 // of clearing the n_zero per-tile pair counters.  Work the step needs
 // anyway, done here instead of in two launches of its own.
-__device__ void project_side_block(const ViewDev* __restrict__ views, int V, int nb,
+__device__ void project_side_block(const ViewDev* __restrict__ views, int V, int c, int v,
                                    const uint8_t* __restrict__ mask, int nmb,
                                    uint32_t* __restrict__ mpart, uint32_t* __restrict__ zero_words,
                                    int64_t n_zero, uint32_t* s_w) {
-  const int c = blockIdx.x - nb, v = blockIdx.y;
   const ViewDev& vw = views[v];
   const int64_t npix = (int64_t)vw.w * vw.h;
   const uint8_t* m = mask + vw.pix_off;
@@ -57,51 +67,50 @@ __device__ void project_side_block(const ViewDev* __restrict__ views, int V, int
     zero_words[k] = 0u;
 }
 
-__global__ __launch_bounds__(kProjBlock) void k_project(
-    const ViewDev* __restrict__ views, int V, int N, int nb, float eps, float qcut,
-    const float* __restrict__ px, const float* __restrict__ py, const float* __restrict__ pz,
-    const float* __restrict__ pq, const float* __restrict__ ps,
-    uint32_t* __restrict__ cnt, float4* __restrict__ rec, uint2* __restrict__ rect,
-    uint16_t* __restrict__ rspan, uint32_t* __restrict__ part, uint32_t* __restrict__ partv,
-    const uint8_t* __restrict__ mask, int nmb,
-    uint32_t* __restrict__ mpart, uint32_t* __restrict__ zero_words, int64_t n_zero) {
-  __shared__ uint32_t s_w[kProjBlock / 64];
-  if (blockIdx.x >= (unsigned)nb) {
-    project_side_block(views, V, nb, mask, nmb, mpart, zero_words, n_zero, s_w);
-    return;
-  }
-  __shared__ uint32_t s_v[kProjBlock / 64];
-  __shared__ Span s_sp[kProjBlock];           // per-record span set-up
-  __shared__ uint32_t s_roff[kProjBlock];     // first row item of each lane in its wave
-  __shared__ uint32_t s_y0[kProjBlock];
-  __shared__ uint32_t s_y1[kProjBlock];
-  __shared__ uint32_t s_cnt[kProjBlock];
-  const int i = blockIdx.x * kProjBlock + threadIdx.x;
-  const int v = blockIdx.y;
+struct ProjLds {
+  uint32_t w[kProjBlock / 64], v[kProjBlock / 64];
+  Span sp[kProjBlock];            // per-record span set-up
+  uint32_t roff[kProjBlock];      // first row item of each lane in its wave
+  uint32_t y0[kProjBlock], y1[kProjBlock], cnt[kProjBlock];
+};
+
+// The projection of one range of surfels into view v.  Surfels that certainly
+// lie outside (the contract's first tests, frustum_outside) skip it, and so do
+// waves and blocks of such surfels.  A block without a candidate does not write
+// its slots' counts: every reader of per-slot arrays tests the block's visible
+// count (partv) first.
+__device__ __forceinline__ void project_block(
+    ProjLds& L, const ViewDev* __restrict__ views, int N, int nb, int range, int v, float eps,
+    float qcut, double r_cut, double sqrt_eps, const float* __restrict__ px,
+    const float* __restrict__ py, const float* __restrict__ pz, const float* __restrict__ pq,
+    const float* __restrict__ ps, uint32_t* __restrict__ cnt, float4* __restrict__ rec,
+    uint2* __restrict__ rect, uint16_t* __restrict__ rspan, uint32_t* __restrict__ part,
+    uint32_t* __restrict__ partv) {
+  const int i = range * kProjBlock + threadIdx.x;
   const int lane = threadIdx.x & 63, wbase = threadIdx.x & ~63;
   const bool valid = i < N;
-  (void)V;
   const ViewDev& vw = views[v];
   const size_t slot = (size_t)v * N + i;
-  // a block none of whose surfels lies in the view's ground rectangle (most
-  // blocks of a long road) is culled whole: the same test the contract takes
-  // first, without the projection, scans and barriers of the full path.  Its
-  // slots' counts are not written: every reader of per-slot arrays tests the
-  // block's visible count (partv) first.
-  if (!__syncthreads_or(valid && ground_inside(vw, px[i], py[i]))) {
-    if (threadIdx.x == 0) {
-      part[(size_t)v * nb + blockIdx.x] = 0u;
-      partv[(size_t)v * nb + blockIdx.x] = 0u;
-    }
+  const size_t pb = (size_t)v * nb + range;
+  float zf = 0.0f, sxf = 0.0f, syf = 0.0f;
+  bool cand = false;
+  if (valid && ground_inside(vw, px[i], py[i])) {
+    zf = pz[i];
+    sxf = ps[i];
+    syf = ps[N + i];
+    cand = !frustum_outside(vw, r_cut, sqrt_eps, px[i], py[i], zf, sxf, syf);
+  }
+  if (!__syncthreads_or(cand)) {
+    if (threadIdx.x == 0) part[pb] = partv[pb] = 0u;
     return;
   }
   uint32_t nt = 0, rows = 0;
   Proj p;
   p.vis = false;
   p.y0 = 0;
-  if (valid) {
-    p = project_contract(vw, eps, qcut, px[i], py[i], pz[i], pq[i], pq[N + i],
-                         pq[2 * (size_t)N + i], pq[3 * (size_t)N + i], ps[i], ps[N + i]);
+  if (cand) {
+    p = project_contract(vw, eps, qcut, px[i], py[i], zf, pq[i], pq[N + i],
+                         pq[2 * (size_t)N + i], pq[3 * (size_t)N + i], sxf, syf);
     if (p.vis) {
       const Span sp = span_setup(p.uh, p.vh, p.ul, p.vl, p.A, p.B, p.C, qcut, p.x0, p.x1);
       if (sp.full) {
@@ -112,7 +121,7 @@ __global__ __launch_bounds__(kProjBlock) void k_project(
       } else {
         rows = (uint32_t)(p.y1 - p.y0);
       }
-      s_sp[threadIdx.x] = sp;
+      L.sp[threadIdx.x] = sp;
       rec[2 * slot] = make_float4(p.uh, p.vh, p.ul, p.vl);
       rec[2 * slot + 1] = make_float4(p.A, p.B, p.C, p.tz);
       rect[slot] = make_uint2((uint32_t)p.x0 | ((uint32_t)p.x1 << 16),
@@ -123,41 +132,154 @@ __global__ __launch_bounds__(kProjBlock) void k_project(
   // of one record are summed into its lane's counter (integer adds)
   const uint32_t incl = wave_incl_scan(rows, lane);
   const uint32_t R = __shfl(incl, 63, 64);
-  s_roff[threadIdx.x] = incl - rows;
-  s_y0[threadIdx.x] = (uint32_t)p.y0;
-  s_y1[threadIdx.x] = (uint32_t)p.y1;
-  s_cnt[threadIdx.x] = 0;
+  L.roff[threadIdx.x] = incl - rows;
+  L.y0[threadIdx.x] = (uint32_t)p.y0;
+  L.y1[threadIdx.x] = (uint32_t)p.y1;
+  L.cnt[threadIdx.x] = 0;
   __syncthreads();
   for (uint32_t k = (uint32_t)lane; k < R; k += 64) {
-    const int j = wbase + last_le(s_roff + wbase, 64, k);
-    const int r = (int)(k - s_roff[j]);
-    const Span& sj = s_sp[j];
+    const int j = wbase + last_le(L.roff + wbase, 64, k);
+    const int r = (int)(k - L.roff[j]);
+    const Span& sj = L.sp[j];
     int lo, hi;
-    span_row(sj, vw.tw, vw.th, vw.w, vw.h, (int)s_y0[j] + r, lo, hi);
-    if (hi > lo) atomicAdd(&s_cnt[j], (uint32_t)(hi - lo));
-    if (span_desc_ok(sj.x0, sj.x1, (int)s_y0[j], (int)s_y1[j]))
-      rspan[((size_t)v * N + blockIdx.x * kProjBlock + (j & (kProjBlock - 1))) * kSpanRows + r] =
+    span_row(sj, vw.tw, vw.th, vw.w, vw.h, (int)L.y0[j] + r, lo, hi);
+    if (hi > lo) atomicAdd(&L.cnt[j], (uint32_t)(hi - lo));
+    if (span_desc_ok(sj.x0, sj.x1, (int)L.y0[j], (int)L.y1[j]))
+      rspan[((size_t)v * N + range * kProjBlock + (j & (kProjBlock - 1))) * kSpanRows + r] =
           (uint16_t)((lo - sj.x0) | ((hi - sj.x0) << 8));
   }
   __syncthreads();
-  nt += s_cnt[threadIdx.x];
+  nt += L.cnt[threadIdx.x];
   if (valid) cnt[slot] = nt;
   uint32_t ws = wave_sum_u32(nt);
   const uint32_t wvis = (uint32_t)__popcll(__ballot(nt != 0));
   if (lane == 0) {
-    s_w[threadIdx.x >> 6] = ws;
-    s_v[threadIdx.x >> 6] = wvis;
+    L.w[threadIdx.x >> 6] = ws;
+    L.v[threadIdx.x >> 6] = wvis;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t t = 0, tv = 0;
     for (int w = 0; w < kProjBlock / 64; ++w) {
-      t += s_w[w];
-      tv += s_v[w];
+      t += L.w[w];
+      tv += L.v[w];
     }
-    part[(size_t)v * nb + blockIdx.x] = t;
-    partv[(size_t)v * nb + blockIdx.x] = tv;
+    part[pb] = t;
+    partv[pb] = tv;
   }
+}
+
+// The (range, view) pairs that the projection has to look at: a wave per range
+// of kProjBlock surfels, four to a lane, tests them against every view's ground
+// rectangle and image (frustum_outside), appends the pairs with a candidate, as
+// index v * nb + range, to list, and writes the zero counts of the others.
+// Most pairs of a long road go here (82 % of 24 views of a 200 m strip, more of
+// a longer one), and a block of the projection's own launch for each of them is
+// bound by the rate at which blocks start (kProjListMin).  Extra blocks as in project_side_block from block
+// range_blocks on.
+__global__ __launch_bounds__(kProjBlock) void k_project_list(
+    const ViewDev* __restrict__ views, int V, int N, int nb, int range_blocks, double r_cut,
+    double sqrt_eps, const float* __restrict__ px, const float* __restrict__ py,
+    const float* __restrict__ pz, const float* __restrict__ ps, uint32_t* __restrict__ part,
+    uint32_t* __restrict__ partv, uint32_t* __restrict__ list, uint32_t* __restrict__ misc,
+    const uint8_t* __restrict__ mask, int nmb, uint32_t* __restrict__ mpart,
+    uint32_t* __restrict__ zero_words, int64_t n_zero) {
+  __shared__ uint32_t s_w[kProjBlock / 64];
+  if (blockIdx.x >= (unsigned)range_blocks) {
+    const int k = (int)blockIdx.x - range_blocks;
+    project_side_block(views, V, k % nmb, k / nmb, mask, nmb, mpart, zero_words, n_zero, s_w);
+    return;
+  }
+  constexpr int kPer = kProjBlock / 64;
+  const int lane = threadIdx.x & 63;
+  const int range = (int)blockIdx.x * kPer + (int)(threadIdx.x >> 6);
+  if (range >= nb) return;
+  const int i0 = range * kProjBlock + lane;
+  float x[kPer], y[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    // (past the end: the range's first surfel once more, which adds no candidate)
+    const int i = i0 + 64 * u < N ? i0 + 64 * u : range * kProjBlock;
+    x[u] = px[i];
+    y[u] = py[i];
+  }
+  for (int v0 = 0; v0 < V; v0 += 64) {
+    // bit k: some surfel of the range may be visible in view v0 + k
+    const int vn = min(64, V - v0);
+    unsigned long long any = 0ull;
+    for (int k = 0; k < vn; ++k) {
+      const ViewDev& vw = views[v0 + k];
+      bool c = false;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) c = c || ground_inside(vw, x[u], y[u]);
+      if (__ballot(c)) any |= 1ull << k;
+    }
+    if (any) {
+      float z[kPer], sx[kPer], sy[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int i = i0 + 64 * u < N ? i0 + 64 * u : range * kProjBlock;
+        z[u] = pz[i];
+        sx[u] = ps[i];
+        sy[u] = ps[N + i];
+      }
+      for (unsigned long long m = any; m; m &= m - 1ull) {
+        const int k = __builtin_ctzll(m);
+        const ViewDev& vw = views[v0 + k];
+        bool c = false;
+        for (int u = 0; u < kPer; ++u)
+          c = c || (ground_inside(vw, x[u], y[u]) &&
+                    !frustum_outside(vw, r_cut, sqrt_eps, x[u], y[u], z[u], sx[u], sy[u]));
+        if (!__ballot(c)) any &= ~(1ull << k);
+      }
+    }
+    uint32_t base = 0;
+    if (lane == 0 && any) base = atomicAdd(&misc[kMiscList], (uint32_t)__popcll(any));
+    base = __shfl(base, 0, 64);
+    if (lane < vn) {
+      const size_t pb = (size_t)(v0 + lane) * nb + range;
+      if ((any >> lane) & 1ull) {
+        list[base + (uint32_t)__popcll(any & ((1ull << lane) - 1ull))] = (uint32_t)pb;
+      } else {
+        part[pb] = 0u;
+        partv[pb] = 0u;
+      }
+    }
+  }
+}
+
+// One (range, view) pair per block: each thread projects one surfel.  With
+// list, the blocks stride over the pairs that k_project_list left; without, the
+// pair is the block's own (grid.x = range, grid.y = view).
+__global__ __launch_bounds__(kProjBlock) void k_project(
+    const ViewDev* __restrict__ views, int V, int N, int nb, float eps, float qcut, double r_cut,
+    double sqrt_eps, const float* __restrict__ px, const float* __restrict__ py,
+    const float* __restrict__ pz,
+    const float* __restrict__ pq, const float* __restrict__ ps,
+    uint32_t* __restrict__ cnt, float4* __restrict__ rec, uint2* __restrict__ rect,
+    uint16_t* __restrict__ rspan, uint32_t* __restrict__ part, uint32_t* __restrict__ partv,
+    const uint32_t* __restrict__ list, const uint32_t* __restrict__ misc,
+    const uint8_t* __restrict__ mask, int nmb,
+    uint32_t* __restrict__ mpart, uint32_t* __restrict__ zero_words, int64_t n_zero) {
+  __shared__ ProjLds L;
+  if (list) {
+    const uint32_t n = misc[kMiscList];
+    for (uint32_t w = blockIdx.x; w < n; w += gridDim.x) {
+      const uint32_t pb = list[w];
+      const int v = (int)(pb / (uint32_t)nb);
+      project_block(L, views, N, nb, (int)(pb - (uint32_t)v * (uint32_t)nb), v, eps, qcut, r_cut,
+                    sqrt_eps, px, py, pz, pq, ps, cnt, rec, rect, rspan, part, partv);
+      __syncthreads();
+    }
+    return;
+  }
+  if (blockIdx.x >= (unsigned)nb) {
+    project_side_block(views, V, (int)blockIdx.x - nb, (int)blockIdx.y, mask, nmb, mpart,
+                       zero_words, n_zero, L.w);
+    return;
+  }
+  project_block(L, views, N, nb, (int)blockIdx.x, (int)blockIdx.y, eps, qcut, r_cut, sqrt_eps, px,
+                py, pz, pq, ps, cnt, rec, rect, rspan, part, partv);
 }
 
 // Feature records of the surfel ranges (projection blocks) that some view sees,
@@ -464,15 +586,28 @@ void launch_project(const Layout& L, void* ws, const rogs_surfels* s, hipStream_
                     const uint8_t* mask) {
   fill_u32(at<uint32_t>(ws, L.o_misc), 0u, kMiscCount, st);
   const int nmb = mask ? mask_chunks(L) : 0;
-  hipLaunchKernelGGL(k_project, dim3(L.nb + nmb, L.V), dim3(kProjBlock), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.N, L.nb, L.eps2d, L.q_cut, s->x, s->y, s->z,
-                     s->q, s->s, at<uint32_t>(ws, L.o_cnt),
-                     at<float4>(ws, L.o_rec), at<uint2>(ws, L.o_rect),
-                     at<uint16_t>(ws, L.o_rspan), at<uint32_t>(ws, L.o_part),
-                     at<uint32_t>(ws, L.o_partv), mask, nmb,
-                     mask ? at<uint32_t>(ws, L.o_mpart) : nullptr,
-                     mask ? at<uint32_t>(ws, L.o_tcnt) : nullptr,
-                     mask ? L.total_tiles : (int64_t)0);
+  const ViewDev* views = at<const ViewDev>(ws, L.o_views);
+  uint32_t* misc = at<uint32_t>(ws, L.o_misc);
+  uint32_t* part = at<uint32_t>(ws, L.o_part);
+  uint32_t* partv = at<uint32_t>(ws, L.o_partv);
+  uint32_t* mpart = mask ? at<uint32_t>(ws, L.o_mpart) : nullptr;
+  uint32_t* tcnt = mask ? at<uint32_t>(ws, L.o_tcnt) : nullptr;
+  const int64_t n_zero = mask ? L.total_tiles : 0;
+  const double r_cut = sqrt((double)L.q_cut) * (1.0 + 1e-9), sqrt_eps = sqrt((double)L.eps2d);
+  const bool listed = (int64_t)L.V * L.nb > kProjListMin;
+  uint32_t* list = listed ? at<uint32_t>(ws, L.o_pos) : nullptr;   // written by the compaction later
+  const int range_blocks = (L.nb + kProjBlock / 64 - 1) / (kProjBlock / 64);
+  if (listed)
+    hipLaunchKernelGGL(k_project_list, dim3((unsigned)(range_blocks + nmb * L.V)),
+                       dim3(kProjBlock), 0, st, views, L.V, L.N, L.nb, range_blocks, r_cut, sqrt_eps, s->x, s->y, s->z, s->s, part, partv,
+                       list, misc, mask, nmb, mpart, tcnt, n_zero);
+  const dim3 grid = listed ? dim3((unsigned)std::min<int64_t>((int64_t)L.V * L.nb, kProjListBlocks))
+                           : dim3(L.nb + nmb, L.V);
+  hipLaunchKernelGGL(k_project, grid, dim3(kProjBlock), 0, st, views, L.V, L.N, L.nb, L.eps2d,
+                     L.q_cut, r_cut, sqrt_eps, s->x, s->y, s->z, s->q, s->s,
+                     at<uint32_t>(ws, L.o_cnt), at<float4>(ws, L.o_rec), at<uint2>(ws, L.o_rect),
+                     at<uint16_t>(ws, L.o_rspan), part, partv, list, misc, mask, nmb, mpart, tcnt,
+                     n_zero);
 }
 
 void launch_pack_feat(const Layout& L, void* ws, const rogs_surfels* s, hipStream_t st) {

@@ -45,6 +45,9 @@ struct ViewDev {
   // 0.65 H / f_y, and 1 / tw, 1 / th (exact: the tile sides are powers of
   // two, so multiplying by them rounds exactly as dividing by the sides)
   double limx, limy, itw, ith;
+  // bounds for frustum_outside: the least upper bound of |dM / ds| per row,
+  // and the image size padded to whole tiles
+  double kx, ky, wpad, hpad;
 };
 
 // Number of semantic classes with a compiled kernel set.
@@ -93,6 +96,7 @@ inline int mask_chunks(const Layout& L) {
 enum MiscSlot {
   kMiscPairs = 0, kMiscOverflow = 1, kMiscVisible = 2, kMiscLong = 3, kMiscEmit = 4,
   kMiscTicketScan = 5,   // last-block ticket of the count-table scan
+  kMiscList = 6,         // (range, view) blocks left by the projection's cull
   kMiscWork = 8,   // two 64-bit work counters (words 8-11)
   kMiscCount = 16
 };
@@ -152,6 +156,36 @@ __device__ inline bool ground_inside(const ViewDev& c, float xf, float yf) {
   const double a = dx * (double)c.ex[0] + dy * (double)c.ex[1];
   const double b = dx * (double)c.ez[0] + dy * (double)c.ez[1];
   return fabs(a) <= (double)c.lat && b >= 0.0 && b <= (double)c.fwd;
+}
+
+// Whether a surfel is certainly not visible by the contract because it lies
+// before the near plane (the contract's own test) or its 3-sigma box misses the
+// padded image.  True only if the contract would cull it, so it may stand
+// before the projection.  The box is bounded without the rotation and without
+// a division: the columns of M are J times vectors of length <= s_x, s_y
+// rotated by R, so sqrt(g0) <= k_x (s_x + s_y) / t_z with k_x = f_x (|R row 0| +
+// lim_x |R row 2|) (orthographic: k_x = f_x |R row 0|, without t_z), and h_x <=
+// r (sqrt(g0) + sqrt(eps)) + 1, r = sqrt(q_cut).  u + h_x < 0 and u - h_x >=
+// padded width are tested multiplied by t_z > 0, with 0.01 px and 1e-12 of the
+// terms for the rounding of both sides.
+__device__ inline bool frustum_outside(const ViewDev& c, double r, double sqrt_eps, float xf,
+                                       float yf, float zf, float sxf, float syf) {
+#pragma clang fp contract(off)
+  const double x = xf, y = yf, z = zf;
+  const double tx = (((double)c.R[0] * x + (double)c.R[1] * y) + (double)c.R[2] * z) + (double)c.t[0];
+  const double ty = (((double)c.R[3] * x + (double)c.R[4] * y) + (double)c.R[5] * z) + (double)c.t[1];
+  const double tz = (((double)c.R[6] * x + (double)c.R[7] * y) + (double)c.R[8] * z) + (double)c.t[2];
+  if (!(tz >= (double)c.znear)) return true;
+  const double zz = c.model == ROGS_PINHOLE ? tz : 1.0;
+  if (!(zz > 0.0)) return false;
+  const double ss = r * ((double)fabsf(sxf) + (double)fabsf(syf));
+  const double pad = (r * sqrt_eps + 1.01) * zz;
+  const double fu = (double)c.fx * tx, cu = (double)c.cx * zz, wu = c.wpad * zz;
+  const double fv = (double)c.fy * ty, cv = (double)c.cy * zz, wv = c.hpad * zz;
+  const double mu = c.kx * ss + pad + 1e-12 * (fabs(fu) + fabs(cu) + wu);
+  const double mv = c.ky * ss + pad + 1e-12 * (fabs(fv) + fabs(cv) + wv);
+  const double pu = fu + cu, pv = fv + cv;
+  return pu + mu < 0.0 || pu - mu > wu || pv + mv < 0.0 || pv - mv > wv;
 }
 
 // Key contract (see rogs.h): the projection in binary64 from the binary32
