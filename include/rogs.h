@@ -441,7 +441,7 @@ ROGS_API int rogs_meshgrid_layout(rogs_ctx* ctx, const rogs_pose* poses, int32_t
  * northern edge.  Every chunk of chunk_px x chunk_px pixels (smaller at the
  * right and bottom edges) is one orthographic camera looking straight down
  * from `height` (rogs_bev_camera), rendered with rogs_project + rogs_bin_sort
- * (host count, one sync per chunk) + rogs_render_fwd and copied into `out`:
+ * (host count, one sync per chunk) + rogs_render_fwd straight into `out`:
  * the planes selected by `channels` (ROGS_CH_* as for serving, in the order
  * RGB, SEM, D, A, ELEV, each W x H floats; ELEV = height - D / A, NaN where
  * A = 0).  ws: device workspace of rogs_bev_workspace_size bytes for the
@@ -511,7 +511,7 @@ ROGS_API int rogs_autotune(rogs_ctx* ctx, const rogs_surfels* s, const rogs_came
  * server batch whatever is queued whenever one is idle (continuous
  * batching, up to max_views views per batch and what a lane's arena holds),
  * renders the batch with rogs_project + rogs_bin_sort (pair count on the
- * device) + rogs_render_fwd, and copies each request's channels into its
+ * device) + rogs_render_fwd, each request's channels straight into its
  * buffer.  A batch that overflows the pair capacity the arena leaves is split
  * in two and rerun; a single view that still does not fit completes with
  * status ROGS_ECAPACITY.  Every view is rendered independently of the rest

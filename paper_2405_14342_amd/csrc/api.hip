@@ -17,11 +17,7 @@ struct rogs_ctx {
   std::string err;
   bool have_batch = false;
   bool sorted = false;
-  // per-view channel sets for the next rogs_project (render server); the
-  // batch's views had sets of their own; the last forward wrote every plane
-  // and the backward's per-pixel state
-  std::vector<uint32_t> view_ch;
-  bool batch_view_ch = false;
+  // the last forward wrote the backward's per-pixel state of every view
   bool fwd_full = false;
   Layout L;
   void* ws = nullptr;
@@ -256,15 +252,6 @@ void ctx_fused_forget(rogs_ctx* c) {
   F.launched = 0;
 }
 
-int ctx_set_view_channels(rogs_ctx* c, const uint32_t* ch, int n) {
-  if (!c || n < 0 || (n > 0 && !ch)) return ROGS_EINVAL;
-  c->view_ch.assign(ch, ch + n);
-  // elevation is formed from depth and alpha
-  for (uint32_t& k : c->view_ch)
-    if (k & ROGS_CH_ELEV) k |= ROGS_CH_D | ROGS_CH_A;
-  return ROGS_OK;
-}
-
 }  // namespace rogs
 
 namespace {
@@ -272,7 +259,7 @@ namespace {
 // Writes the device view table and the per-view first loss-block table of a
 // batch into host memory at dst (sizeof(ViewDev) * V + 8 * (V + 1) bytes).
 void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
-                     const uint32_t* ch = nullptr) {
+                     const rogs::ViewOut* vo = nullptr) {
   const size_t vbytes = sizeof(ViewDev) * L.V;
   ViewDev* vt = static_cast<ViewDev*>(dst);
   int64_t* fb = reinterpret_cast<int64_t*>(static_cast<char*>(dst) + vbytes);
@@ -313,7 +300,14 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
     d.wpad = (double)d.tiles_x * vtw;
     d.hpad = (double)d.tiles_y * vth;
     d.tile_off = (int32_t)tiles;
-    d.ch = ch ? ch[v] : (uint32_t)ROGS_CH_ALL;
+    d.ch = (uint32_t)ROGS_CH_ALL;
+    if (vo) {
+      d.ch = vo[v].ch;
+      d.out = vo[v].out;
+      d.out_plane = vo[v].plane;
+      d.out_row = vo[v].row;
+      d.elev_ref = vo[v].elev_ref;
+    }
     vt[v] = d;
     fb[v] = blk;
     pix += (int64_t)k.w * k.h;
@@ -323,7 +317,8 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
   fb[L.V] = blk;
 }
 
-int upload_views(rogs_ctx* c, const Layout& L, const rogs_camera* cams, void* ws, hipStream_t st) {
+int upload_views(rogs_ctx* c, const Layout& L, const rogs_camera* cams, void* ws, hipStream_t st,
+                 const rogs::ViewOut* outs = nullptr) {
   const size_t vbytes = sizeof(ViewDev) * L.V;
   const size_t fbytes = sizeof(int64_t) * (L.V + 1);
   const size_t need = vbytes + fbytes;
@@ -340,10 +335,7 @@ int upload_views(rogs_ctx* c, const Layout& L, const rogs_camera* cams, void* ws
     if (e != hipSuccess) return hip_fail(c, e, "hipHostMalloc");
     c->stage_bytes = need;
   }
-  const bool own = c->view_ch.size() == (size_t)L.V;
-  fill_view_table(L, cams, c->stage, own ? c->view_ch.data() : nullptr);
-  c->batch_view_ch = own;
-  c->view_ch.clear();
+  fill_view_table(L, cams, c->stage, outs);
   hipError_t e = hipMemcpyAsync(rogs::at<void>(ws, L.o_views), c->stage, vbytes + fbytes,
                                 hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipEventRecord(c->stage_evt, st);
@@ -427,7 +419,76 @@ int check_surfels(rogs_ctx* c, const rogs_surfels* s, const Layout& L) {
   return ROGS_OK;
 }
 
+int project_batch(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
+                  const rogs_render_opts* opts, void* ws, size_t ws_bytes, int64_t pair_capacity,
+                  int64_t slot_capacity, void* stream, const rogs::ViewOut* outs) {
+  if (!c) return ROGS_EINVAL;
+  Layout L;
+  const char* why = nullptr;
+  int r = rogs::make_layout(s, cams, n_views, opts, pair_capacity, slot_capacity, &L, &why);
+  if (r != ROGS_OK) return fail(c, r, why ? why : "invalid argument");
+  r = check_surfels(c, s, L);
+  if (r != ROGS_OK) return r;
+  if (!ws) return fail(c, ROGS_EINVAL, "workspace is null");
+  if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(c, ROGS_EINVAL, "workspace must be 256-byte aligned");
+  if (ws_bytes < L.total)
+    return fail(c, ROGS_ENOMEM, "workspace too small: need " + std::to_string(L.total) + " bytes");
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  c->have_batch = false;
+  c->sorted = false;
+  c->fwd_full = false;
+  r = upload_views(c, L, cams, ws, st, outs);
+  if (r != ROGS_OK) return r;
+  prof_begin(c, 0, st);
+  rogs::launch_project(L, ws, s, st);
+  rogs::launch_pack_feat(L, ws, s, st);
+  prof_end(c, st);
+  prof_begin(c, 1, st);
+  rogs::launch_scan_part(L, ws, st);
+  prof_end(c, st);
+  r = check_launch(c, "rogs_project");
+  if (r != ROGS_OK) return r;
+  c->L = L;
+  c->ws = ws;
+  c->have_batch = true;
+  c->n_pairs_host = -1;
+  return ROGS_OK;
+}
+
+// Composites the batch into out_images, or into the views' own outputs if that
+// is null; save keeps the per-pixel state of the backward.
+int render_batch(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_images, uint32_t mask,
+                 bool save, void* stream) {
+  // elevation is formed from depth and alpha
+  const uint32_t ch = mask & ROGS_CH_ELEV ? mask | ROGS_CH_D | ROGS_CH_A : mask;
+  constexpr uint32_t kPlanes = ROGS_CH_RGB | ROGS_CH_SEM | ROGS_CH_D | ROGS_CH_A;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  prof_begin(c, 5, st);
+  int rr = rogs::launch_render_fwd(c->L, ws, s, out_images, mask, save, st);
+  c->fwd_full = save && (ch & kPlanes) == kPlanes;
+  prof_end(c, st);
+  if (rr != 0) return fail(c, ROGS_EINVAL, "unsupported n_sem / tile shape");
+  return check_launch(c, "rogs_render_fwd");
+}
+
 }  // namespace
+
+namespace rogs {
+
+int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
+                    const rogs_render_opts* opts, void* ws, size_t ws_bytes,
+                    int64_t pair_capacity, void* stream, const ViewOut* outs) {
+  return project_batch(c, s, cams, n_views, opts, ws, ws_bytes, pair_capacity, 0, stream, outs);
+}
+
+int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, uint32_t mask, bool save,
+                   void* stream) {
+  int r = need_batch(c, ws, true);
+  if (r == ROGS_OK) r = check_surfels(c, s, c->L);
+  return r == ROGS_OK ? render_batch(c, s, ws, nullptr, mask, save, stream) : r;
+}
+
+}  // namespace rogs
 
 extern "C" {
 
@@ -496,37 +557,8 @@ int rogs_workspace_size(const rogs_surfels* s, const rogs_camera* cams, int32_t 
 int rogs_project(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
                  const rogs_render_opts* opts, void* ws, size_t ws_bytes, int64_t pair_capacity,
                  int64_t slot_capacity, void* stream) {
-  if (!c) return ROGS_EINVAL;
-  Layout L;
-  const char* why = nullptr;
-  int r = rogs::make_layout(s, cams, n_views, opts, pair_capacity, slot_capacity, &L, &why);
-  if (r != ROGS_OK) return fail(c, r, why ? why : "invalid argument");
-  r = check_surfels(c, s, L);
-  if (r != ROGS_OK) return r;
-  if (!ws) return fail(c, ROGS_EINVAL, "workspace is null");
-  if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(c, ROGS_EINVAL, "workspace must be 256-byte aligned");
-  if (ws_bytes < L.total)
-    return fail(c, ROGS_ENOMEM, "workspace too small: need " + std::to_string(L.total) + " bytes");
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  c->have_batch = false;
-  c->sorted = false;
-  c->fwd_full = false;
-  r = upload_views(c, L, cams, ws, st);
-  if (r != ROGS_OK) return r;
-  prof_begin(c, 0, st);
-  rogs::launch_project(L, ws, s, st);
-  rogs::launch_pack_feat(L, ws, s, st);
-  prof_end(c, st);
-  prof_begin(c, 1, st);
-  rogs::launch_scan_part(L, ws, st);
-  prof_end(c, st);
-  r = check_launch(c, "rogs_project");
-  if (r != ROGS_OK) return r;
-  c->L = L;
-  c->ws = ws;
-  c->have_batch = true;
-  c->n_pairs_host = -1;
-  return ROGS_OK;
+  return project_batch(c, s, cams, n_views, opts, ws, ws_bytes, pair_capacity, slot_capacity,
+                       stream, nullptr);
 }
 
 int rogs_pair_count(rogs_ctx* c, void* ws, int64_t* n_pairs, int32_t* overflow, void* stream) {
@@ -627,17 +659,7 @@ int rogs_render_fwd(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_ima
   if (!out_images) return fail(c, ROGS_EINVAL, "out_images is null");
   if (channel_mask == 0u || (channel_mask & ~(uint32_t)ROGS_CH_ALL) != 0u)
     return fail(c, ROGS_EINVAL, "channel_mask must be a non-empty OR of ROGS_CH_* bits");
-  // elevation is formed from depth and alpha
-  uint32_t mask = channel_mask;
-  if (mask & ROGS_CH_ELEV) mask |= ROGS_CH_D | ROGS_CH_A;
-  constexpr uint32_t kPlanes = ROGS_CH_RGB | ROGS_CH_SEM | ROGS_CH_D | ROGS_CH_A;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  prof_begin(c, 5, st);
-  int rr = rogs::launch_render_fwd(c->L, ws, s, out_images, mask, st);
-  c->fwd_full = (mask & kPlanes) == kPlanes && !c->batch_view_ch;
-  prof_end(c, st);
-  if (rr != 0) return fail(c, ROGS_EINVAL, "unsupported n_sem / tile shape");
-  return check_launch(c, "rogs_render_fwd");
+  return render_batch(c, s, ws, out_images, channel_mask, true, stream);
 }
 
 int rogs_debug_work(rogs_ctx* c, void* ws, int64_t* evaluated, int64_t* contributing,

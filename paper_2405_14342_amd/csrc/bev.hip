@@ -1,41 +1,13 @@
 // Chunked orthographic BEV export (Sec. 4.2 "rendered in chunks and then
 // stitched"; supp. Sec. 2.2): the map's top-down image is covered by square
 // orthographic cameras of chunk_px x chunk_px pixels; each is rendered with
-// the same project / bin / composite calls as training and copied into its
-// place in the stitched image, together with the elevation (camera height
-// minus the opacity-weighted depth).
+// the same project / bin / composite calls as training straight into its place
+// in the stitched image, together with the elevation (camera height minus the
+// opacity-weighted depth).
 #include <algorithm>
 #include <string>
 
 #include "rogs_internal.h"
-
-namespace {
-
-// Copies the requested planes of one rendered chunk (5 + C planes) into the
-// stitched image (planes of W x H) at column ox, row oy.
-__global__ __launch_bounds__(256) void k_stitch(const float* __restrict__ img, int cw, int ch,
-                                                int C, uint32_t chans, float elev_ref,
-                                                float* __restrict__ out, int W, int H, int ox,
-                                                int oy) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t np = (int64_t)cw * ch;
-  if (p >= np) return;
-  const int u = (int)(p % cw), v = (int)(p / cw);
-  const int64_t g = (int64_t)(oy + v) * W + (ox + u);
-  const int64_t GP = (int64_t)W * H;
-  int o = 0;
-  if (chans & ROGS_CH_RGB)
-    for (int c = 0; c < 3; ++c) out[(o++) * GP + g] = img[c * np + p];
-  if (chans & ROGS_CH_SEM)
-    for (int c = 0; c < C; ++c) out[(o++) * GP + g] = img[(3 + c) * np + p];
-  const float D = img[(3 + C) * np + p], A = img[(4 + C) * np + p];
-  if (chans & ROGS_CH_D) out[(o++) * GP + g] = D;
-  if (chans & ROGS_CH_A) out[(o++) * GP + g] = A;
-  if (chans & ROGS_CH_ELEV)
-    out[(o++) * GP + g] = (A > 0.0f) ? elev_ref - D / A : __int_as_float(0x7fc00000);
-}
-
-}  // namespace
 
 extern "C" {
 
@@ -87,7 +59,6 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
   int r = rogs_bev_workspace_size(s, chunk_px, opts, pair_capacity, &need);
   if (r != ROGS_OK) return rogs::ctx_fail(c, r, "rogs_bev_export: invalid surfels or options");
   if (ws_bytes < need) return rogs::ctx_fail(c, ROGS_ENOMEM, "rogs_bev_export: workspace too small");
-  hipStream_t st = static_cast<hipStream_t>(stream);
   int64_t worst = 0;
   for (int oy = 0; oy < H; oy += chunk_px) {
     for (int ox = 0; ox < W; ox += chunk_px) {
@@ -97,22 +68,17 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
       size_t wsb = 0;
       r = rogs_workspace_size(s, &cam, 1, opts, pair_capacity, 0, &wsb);
       if (r != ROGS_OK) return rogs::ctx_fail(c, r, "rogs_bev_export: chunk layout");
-      float* img = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + (wsb + 255) / 256 * 256);
-      r = rogs_project(c, s, &cam, 1, opts, ws, wsb, pair_capacity, 0, stream);
+      const rogs::ViewOut vo{(uint32_t)ROGS_CH_ALL, out + (int64_t)oy * W + ox, (int64_t)W * H, W,
+                             height};
+      r = rogs::ctx_project_own(c, s, &cam, 1, opts, ws, wsb, pair_capacity, stream, &vo);
       int64_t n = 0;
       if (r == ROGS_OK) r = rogs_bin_sort(c, ws, &n, ROGS_SYNC_COUNT, stream);
       worst = std::max(worst, n);
       if (n_pairs_max) *n_pairs_max = worst;
       if (r != ROGS_OK) return r;
       // only the planes the export asks for are composited
-      r = rogs_render_fwd(c, s, ws, img, channels, stream);
+      r = rogs::ctx_render_own(c, s, ws, channels, true, stream);
       if (r != ROGS_OK) return r;
-      const int64_t np = (int64_t)cw * ch;
-      hipLaunchKernelGGL(k_stitch, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, img, cw,
-                         ch, s->n_sem, channels, height, out, W, H, ox, oy);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess)
-        return rogs::ctx_fail(c, ROGS_EHIP, std::string("rogs_bev_export: ") + hipGetErrorString(e));
     }
   }
   return ROGS_OK;

@@ -38,7 +38,7 @@ struct ViewDev {
   int32_t w, h, model;
   int32_t tiles_x, tiles_y;
   int32_t tile_off;     // first global tile index of the view
-  uint32_t ch;          // ROGS_CH_* planes to composite (rogs_render_fwd ANDs its mask)
+  uint32_t ch;          // ROGS_CH_* planes to write (the forward ANDs its mask)
   int16_t tw, th;       // the view's tile shape (tw divides 64; tw * th is the batch's tile area)
   // binary64 constants of the key contract, formed on the host with the
   // contract's own operations: the pinhole clamp limits 0.65 W / f_x and
@@ -48,6 +48,20 @@ struct ViewDev {
   // bounds for frustum_outside: the least upper bound of |dM / ds| per row,
   // and the image size padded to whole tiles
   double kx, ky, wpad, hpad;
+  // the view's own output (ViewOut), used by ctx_render_own
+  float* out;
+  int64_t out_plane, out_row;
+  float elev_ref;
+};
+
+// The output of one view of a served batch or an export: the planes of ch
+// (ROGS_CH_*, in the order RGB, SEM, D, A, ELEV), pixel (x, y) of plane k at
+// out[k plane + y row + x].
+struct ViewOut {
+  uint32_t ch;
+  float* out;
+  int64_t plane, row;
+  float elev_ref;
 };
 
 // Number of semantic classes with a compiled kernel set.
@@ -757,15 +771,19 @@ void launch_layout_fill(const rogs_pose* poses, int np, double x0, double y0, fl
                         int H, void* scratch, int64_t n, int32_t* idx, float* x, float* y,
                         float* z, float* q, int32_t* nbr, hipStream_t st);
 int launch_render_fwd(const Layout& L, void* ws, const rogs_surfels* s, float* out, uint32_t mask,
-                      hipStream_t st);
-// Channel sets (ROGS_CH_*) of the views of the next rogs_project call on this
-// context (n entries, one per view; n = 0 clears: every view gets all
-// planes).  Used by the render server for per-request channel sets.
+                      bool save, hipStream_t st);
 // Waits for the fused steps in flight and forgets them and the captured
 // graph: the next rogs_step_fused starts afresh and rogs_fused_status reports
 // no step until then.
 void ctx_fused_forget(rogs_ctx* c);
-int ctx_set_view_channels(rogs_ctx* c, const uint32_t* ch, int n);
+// rogs_project of views with outputs of their own (one ViewOut per view), and
+// the forward that writes them: of each view the planes of its ch and mask.
+// save keeps the per-pixel state that rogs_render_bwd needs.
+int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
+                    const rogs_render_opts* opts, void* ws, size_t ws_bytes,
+                    int64_t pair_capacity, void* stream, const ViewOut* outs);
+int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, uint32_t mask, bool save,
+                   void* stream);
 void launch_loss(const Layout& L, void* ws, const float* out, const rogs_targets* t, float* G,
                  float* loss_out, float* d_exp, hipStream_t st);
 int launch_render_bwd(const Layout& L, void* ws, const rogs_surfels* s, const float* out,

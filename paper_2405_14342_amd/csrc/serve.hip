@@ -8,9 +8,8 @@
 // arrive while other batches are on the GPU start on a free lane and their
 // work overlaps on the device.  A lane renders its requests as one batch
 // (rogs_project + rogs_bin_sort with the pair count on the device +
-// rogs_render_fwd into its arena share, each view compositing only the planes
-// its request asked for), copies each request's channels into its buffer, and
-// waits for the batch.  If the batch overflowed the pair
+// a forward with each view compositing only the planes its request asked for
+// and writing them into the request's buffer) and waits for the batch.  If the batch overflowed the pair
 // capacity that the arena allows, it is split in two and both halves run
 // again; a single view that does not fit fails with ROGS_ECAPACITY.  Each
 // view is rendered independently of the others in its batch (per-view tile
@@ -33,26 +32,6 @@ int64_t now_ns() {
   return std::chrono::duration_cast<std::chrono::nanoseconds>(
              std::chrono::steady_clock::now().time_since_epoch())
       .count();
-}
-
-// Copies the requested planes of one rendered view (5 + C planes: R G B,
-// sem, D, A) into the request's buffer, in the order RGB, SEM, D, A, ELEV.
-// ELEV = elev_ref - D / A where A > 0, NaN where nothing was composited.
-__global__ __launch_bounds__(256) void k_serve_extract(const float* __restrict__ img, int64_t npix,
-                                                       int C, uint32_t ch, float elev_ref,
-                                                       float* __restrict__ out) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= npix) return;
-  int o = 0;
-  if (ch & ROGS_CH_RGB)
-    for (int c = 0; c < 3; ++c) out[(o++) * npix + p] = img[c * npix + p];
-  if (ch & ROGS_CH_SEM)
-    for (int c = 0; c < C; ++c) out[(o++) * npix + p] = img[(3 + c) * npix + p];
-  const float D = img[(3 + C) * npix + p], A = img[(4 + C) * npix + p];
-  if (ch & ROGS_CH_D) out[(o++) * npix + p] = D;
-  if (ch & ROGS_CH_A) out[(o++) * npix + p] = A;
-  if (ch & ROGS_CH_ELEV)
-    out[(o++) * npix + p] = (A > 0.0f) ? elev_ref - D / A : __int_as_float(0x7fc00000);
 }
 
 struct Item {
@@ -120,6 +99,7 @@ int64_t fit_capacity(const rogs_server* s, const std::vector<rogs_camera>& cams,
 }
 
 // Renders one batch on a lane; returns false if it overflowed and must be split.
+// A batch is sized as if its images were kept in the arena as well.
 bool run_batch(rogs_server* s, ServeLane& ln, std::vector<Item>& batch) {
   std::vector<rogs_camera> cams;
   int64_t pix = 0;
@@ -154,25 +134,15 @@ bool run_batch(rogs_server* s, ServeLane& ln, std::vector<Item>& batch) {
   size_t wsb = 0;
   (void)rogs_workspace_size(&s->map, cams.data(), (int)cams.size(), &s->opts, cap, 0, &wsb);
   void* ws = ln.arena;
-  float* images = reinterpret_cast<float*>(ln.arena + wsb);
-  // each view composites only the planes its request asked for
-  std::vector<uint32_t> chans;
-  for (const Item& it : batch) chans.push_back(it.req.channels);
-  int r = rogs::ctx_set_view_channels(ln.ctx, chans.data(), (int)chans.size());
-  if (r == ROGS_OK)
-    r = rogs_project(ln.ctx, &s->map, cams.data(), (int)cams.size(), &s->opts, ws, wsb, cap, 0,
-                     ln.st);
+  // each view composites only the planes its request asked for, into its buffer
+  std::vector<rogs::ViewOut> outs;
+  for (const Item& it : batch)
+    outs.push_back({it.req.channels, it.req.out, (int64_t)it.req.cam.w * it.req.cam.h,
+                    it.req.cam.w, it.req.elev_ref});
+  int r = rogs::ctx_project_own(ln.ctx, &s->map, cams.data(), (int)cams.size(), &s->opts, ws, wsb,
+                                cap, ln.st, outs.data());
   if (r == ROGS_OK) r = rogs_bin_sort(ln.ctx, ws, nullptr, 0u, ln.st);
-  if (r == ROGS_OK) r = rogs_render_fwd(ln.ctx, &s->map, ws, images, ROGS_CH_ALL, ln.st);
-  int64_t off = 0;
-  const int C = s->map.n_sem;
-  for (size_t k = 0; k < batch.size() && r == ROGS_OK; ++k) {
-    const rogs_request& q = batch[k].req;
-    const int64_t np = (int64_t)q.cam.w * q.cam.h;
-    hipLaunchKernelGGL(k_serve_extract, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, ln.st,
-                       images + (5 + C) * off, np, C, q.channels, q.elev_ref, q.out);
-    off += np;
-  }
+  if (r == ROGS_OK) r = rogs::ctx_render_own(ln.ctx, &s->map, ws, ROGS_CH_ALL, false, ln.st);
   if (r == ROGS_OK && hipGetLastError() != hipSuccess) r = ROGS_EHIP;
   int64_t n = 0;
   int32_t ovf = 0;
