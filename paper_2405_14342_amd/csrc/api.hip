@@ -263,6 +263,7 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
   const size_t vbytes = sizeof(ViewDev) * L.V;
   ViewDev* vt = static_cast<ViewDev*>(dst);
   int64_t* fb = reinterpret_cast<int64_t*>(static_cast<char*>(dst) + vbytes);
+  rogs::ViewOutDev* vd = reinterpret_cast<rogs::ViewOutDev*>(fb + L.V + 1);
   int64_t pix = 0, tiles = 0, blk = 0;
   for (int v = 0; v < L.V; ++v) {
     const rogs_camera& k = cams[v];
@@ -286,8 +287,8 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
     // binary64, and the exact reciprocals of the tile sides
     d.limx = (0.65 * (double)k.w) / (double)k.fx;
     d.limy = (0.65 * (double)k.h) / (double)k.fy;
-    d.itw = 1.0 / (double)vtw;
-    d.ith = 1.0 / (double)vth;
+    d.itw = 1.0f / (float)vtw;
+    d.ith = 1.0f / (float)vth;
     d.tiles_x = (k.w + vtw - 1) / vtw;
     d.tiles_y = (k.h + vth - 1) / vth;
     double rn[3];
@@ -295,18 +296,14 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
       rn[j] = sqrt((double)k.R_cw[3 * j] * k.R_cw[3 * j] + (double)k.R_cw[3 * j + 1] * k.R_cw[3 * j + 1] +
                    (double)k.R_cw[3 * j + 2] * k.R_cw[3 * j + 2]);
     const bool pin = k.model == ROGS_PINHOLE;
-    d.kx = 1.000001 * (double)k.fx * (rn[0] + (pin ? d.limx * rn[2] : 0.0));
-    d.ky = 1.000001 * (double)k.fy * (rn[1] + (pin ? d.limy * rn[2] : 0.0));
-    d.wpad = (double)d.tiles_x * vtw;
-    d.hpad = (double)d.tiles_y * vth;
+    d.kx = (float)(1.000001 * (double)k.fx * (rn[0] + (pin ? d.limx * rn[2] : 0.0)));
+    d.ky = (float)(1.000001 * (double)k.fy * (rn[1] + (pin ? d.limy * rn[2] : 0.0)));
     d.tile_off = (int32_t)tiles;
     d.ch = (uint32_t)ROGS_CH_ALL;
     if (vo) {
       d.ch = vo[v].ch;
-      d.out = vo[v].out;
-      d.out_plane = vo[v].plane;
-      d.out_row = vo[v].row;
-      d.elev_ref = vo[v].elev_ref;
+      const uintptr_t p = reinterpret_cast<uintptr_t>(vo[v].out);
+      vd[v] = {(uint32_t)p, (uint32_t)(p >> 32), vo[v].elev_ref};
     }
     vt[v] = d;
     fb[v] = blk;
@@ -320,7 +317,7 @@ void fill_view_table(const Layout& L, const rogs_camera* cams, void* dst,
 int upload_views(rogs_ctx* c, const Layout& L, const rogs_camera* cams, void* ws, hipStream_t st,
                  const rogs::ViewOut* outs = nullptr) {
   const size_t vbytes = sizeof(ViewDev) * L.V;
-  const size_t fbytes = sizeof(int64_t) * (L.V + 1);
+  const size_t fbytes = sizeof(int64_t) * (L.V + 1) + (outs ? sizeof(rogs::ViewOutDev) * L.V : 0);
   const size_t need = vbytes + fbytes;
   if (c->stage_pending) {
     hipError_t e = hipEventSynchronize(c->stage_evt);
@@ -456,16 +453,16 @@ int project_batch(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, i
 }
 
 // Composites the batch into out_images, or into the views' own outputs if that
-// is null; save keeps the per-pixel state of the backward.
-int render_batch(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_images, uint32_t mask,
-                 bool save, void* stream) {
+// is null.
+int render_batch(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_images,
+                 const rogs::FwdArgs& f, void* stream) {
   // elevation is formed from depth and alpha
-  const uint32_t ch = mask & ROGS_CH_ELEV ? mask | ROGS_CH_D | ROGS_CH_A : mask;
+  const uint32_t ch = f.mask & ROGS_CH_ELEV ? f.mask | ROGS_CH_D | ROGS_CH_A : f.mask;
   constexpr uint32_t kPlanes = ROGS_CH_RGB | ROGS_CH_SEM | ROGS_CH_D | ROGS_CH_A;
   hipStream_t st = static_cast<hipStream_t>(stream);
   prof_begin(c, 5, st);
-  int rr = rogs::launch_render_fwd(c->L, ws, s, out_images, mask, save, st);
-  c->fwd_full = save && (ch & kPlanes) == kPlanes;
+  int rr = rogs::launch_render_fwd(c->L, ws, s, out_images, f, st);
+  c->fwd_full = f.save && (ch & kPlanes) == kPlanes;
   prof_end(c, st);
   if (rr != 0) return fail(c, ROGS_EINVAL, "unsupported n_sem / tile shape");
   return check_launch(c, "rogs_render_fwd");
@@ -481,11 +478,11 @@ int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams,
   return project_batch(c, s, cams, n_views, opts, ws, ws_bytes, pair_capacity, 0, stream, outs);
 }
 
-int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, uint32_t mask, bool save,
+int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, const FwdArgs& fa,
                    void* stream) {
   int r = need_batch(c, ws, true);
   if (r == ROGS_OK) r = check_surfels(c, s, c->L);
-  return r == ROGS_OK ? render_batch(c, s, ws, nullptr, mask, save, stream) : r;
+  return r == ROGS_OK ? render_batch(c, s, ws, nullptr, fa, stream) : r;
 }
 
 }  // namespace rogs
@@ -659,7 +656,7 @@ int rogs_render_fwd(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_ima
   if (!out_images) return fail(c, ROGS_EINVAL, "out_images is null");
   if (channel_mask == 0u || (channel_mask & ~(uint32_t)ROGS_CH_ALL) != 0u)
     return fail(c, ROGS_EINVAL, "channel_mask must be a non-empty OR of ROGS_CH_* bits");
-  return render_batch(c, s, ws, out_images, channel_mask, true, stream);
+  return render_batch(c, s, ws, out_images, {channel_mask, true, 0, 0}, stream);
 }
 
 int rogs_debug_work(rogs_ctx* c, void* ws, int64_t* evaluated, int64_t* contributing,

@@ -68,8 +68,7 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
       size_t wsb = 0;
       r = rogs_workspace_size(s, &cam, 1, opts, pair_capacity, 0, &wsb);
       if (r != ROGS_OK) return rogs::ctx_fail(c, r, "rogs_bev_export: chunk layout");
-      const rogs::ViewOut vo{(uint32_t)ROGS_CH_ALL, out + (int64_t)oy * W + ox, (int64_t)W * H, W,
-                             height};
+      const rogs::ViewOut vo{(uint32_t)ROGS_CH_ALL, out + (int64_t)oy * W + ox, height};
       r = rogs::ctx_project_own(c, s, &cam, 1, opts, ws, wsb, pair_capacity, stream, &vo);
       int64_t n = 0;
       if (r == ROGS_OK) r = rogs_bin_sort(c, ws, &n, ROGS_SYNC_COUNT, stream);
@@ -77,7 +76,7 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
       if (n_pairs_max) *n_pairs_max = worst;
       if (r != ROGS_OK) return r;
       // only the planes the export asks for are composited
-      r = rogs::ctx_render_own(c, s, ws, channels, true, stream);
+      r = rogs::ctx_render_own(c, s, ws, {channels, true, (int64_t)W * H, W}, stream);
       if (r != ROGS_OK) return r;
     }
   }

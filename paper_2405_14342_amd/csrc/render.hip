@@ -840,7 +840,7 @@ __global__ __launch_bounds__(64 * NW) void k_render_fwd(
     float teps, const uint4* __restrict__ tinfo, const uint32_t* __restrict__ spair,
     const float4* __restrict__ rec, const float4* __restrict__ feat, float* __restrict__ out,
     float* __restrict__ tfin, uint32_t* __restrict__ nlast, float2* __restrict__ drel,
-    uint32_t mask) {
+    uint32_t mask, const ViewOutDev* __restrict__ outs, int64_t plane, int64_t row) {
   constexpr int F = 3 + C;
   constexpr int FS4 = (F + 4) / 4;
   constexpr int NO = 5 + C;           // output channels
@@ -863,8 +863,10 @@ __global__ __launch_bounds__(64 * NW) void k_render_fwd(
   const float t0 = p.t0 < FLT_MAX ? p.t0 : 0.0f;           // 0 where nothing contributed
   const float depth = __builtin_fmaf(t0, al, p.acc[F]);    // D = D' + t0 A
   const bool own = out == nullptr;
-  const size_t P = own ? (size_t)tg.vw->out_plane : (size_t)tg.W * tg.H;
-  float* o = own ? tg.vw->out + (size_t)tg.py * (size_t)tg.vw->out_row + tg.px
+  const size_t P = plane ? (size_t)plane : (size_t)tg.W * tg.H;
+  const ViewOutDev* vo = outs + (tg.vw - views);
+  float* o = own ? reinterpret_cast<float*>((uint64_t)vo->lo | (uint64_t)vo->hi << 32) +
+                       (size_t)tg.py * (plane ? (size_t)row : (size_t)tg.W) + tg.px
                  : out + (size_t)NO * tg.vw->pix_off + pix;
   const uint32_t wr = own ? want : ch;      // a view's own output has no other planes
   if (wr & ROGS_CH_RGB)
@@ -880,7 +882,7 @@ __global__ __launch_bounds__(64 * NW) void k_render_fwd(
   if (wr & ROGS_CH_A) *o = al;
   if (own && (wr & ROGS_CH_ELEV)) {
     if (wr & ROGS_CH_A) o += P;
-    *o = al > 0.0f ? tg.vw->elev_ref - depth / al : __int_as_float(0x7fc00000);
+    *o = al > 0.0f ? vo->elev_ref - depth / al : __int_as_float(0x7fc00000);
   }
   if (tfin && (ch & kPlanes) == kPlanes) {
     tfin[tg.vw->pix_off + pix] = p.T;
@@ -1127,15 +1129,16 @@ __global__ __launch_bounds__(64) void k_count_work(
 }
 
 template <int C, int NW>
-void fwd_launch(const Layout& L, void* ws, float* out, uint32_t mask, bool save,
-                hipStream_t st) {
+void fwd_launch(const Layout& L, void* ws, float* out, const FwdArgs& fa, hipStream_t st) {
   hipLaunchKernelGGL((k_render_fwd<C, NW>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0, st,
                      at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
                      L.t_eps, at<const uint4>(ws, L.o_tinfo),
                      at<const uint32_t>(ws, L.o_spair),
                      at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out,
-                     save ? at<float>(ws, L.o_tfin) : nullptr, at<uint32_t>(ws, L.o_nlast),
-                     at<float2>(ws, L.o_drel), mask);
+                     fa.save ? at<float>(ws, L.o_tfin) : nullptr, at<uint32_t>(ws, L.o_nlast),
+                     at<float2>(ws, L.o_drel), fa.mask,
+                     reinterpret_cast<const ViewOutDev*>(at<int64_t>(ws, L.o_lpart) + L.V + 1), fa.plane,
+                     fa.row);
 }
 
 template <int C, int NW, int KS>
@@ -1169,9 +1172,9 @@ void launch_one(const Layout& L, void* ws, const float* out, const float* G, con
 
 template <int C, int NW>
 int dispatch_stage(const Layout& L, void* ws, const float* out, const float* G, float* outw,
-                   const FusedLoss* fl, int which, uint32_t mask, bool save, hipStream_t st) {
+                   const FusedLoss* fl, int which, const FwdArgs& fa, hipStream_t st) {
   if (which == 0) {
-    fwd_launch<C, NW>(L, ws, outw, mask, save, st);
+    fwd_launch<C, NW>(L, ws, outw, fa, st);
     return 0;
   }
   switch (L.stage) {
@@ -1184,43 +1187,43 @@ int dispatch_stage(const Layout& L, void* ws, const float* out, const float* G, 
 
 template <int C>
 int dispatch_waves(const Layout& L, void* ws, const float* out, const float* G, float* outw,
-                   const FusedLoss* fl, int which, uint32_t mask, bool save, hipStream_t st) {
+                   const FusedLoss* fl, int which, const FwdArgs& fa, hipStream_t st) {
   switch (L.nw) {
-    case 1: return dispatch_stage<C, 1>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 2: return dispatch_stage<C, 2>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 4: return dispatch_stage<C, 4>(L, ws, out, G, outw, fl, which, mask, save, st);
+    case 1: return dispatch_stage<C, 1>(L, ws, out, G, outw, fl, which, fa, st);
+    case 2: return dispatch_stage<C, 2>(L, ws, out, G, outw, fl, which, fa, st);
+    case 4: return dispatch_stage<C, 4>(L, ws, out, G, outw, fl, which, fa, st);
     default: return -1;
   }
 }
 
 int dispatch(const Layout& L, void* ws, const float* out, const float* G, float* outw,
-             const FusedLoss* fl, int which, uint32_t mask, bool save, hipStream_t st) {
+             const FusedLoss* fl, int which, const FwdArgs& fa, hipStream_t st) {
   switch (L.C) {
-    case 1: return dispatch_waves<1>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 2: return dispatch_waves<2>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 3: return dispatch_waves<3>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 4: return dispatch_waves<4>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 5: return dispatch_waves<5>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 6: return dispatch_waves<6>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 7: return dispatch_waves<7>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 8: return dispatch_waves<8>(L, ws, out, G, outw, fl, which, mask, save, st);
-    case 16: return dispatch_waves<16>(L, ws, out, G, outw, fl, which, mask, save, st);
+    case 1: return dispatch_waves<1>(L, ws, out, G, outw, fl, which, fa, st);
+    case 2: return dispatch_waves<2>(L, ws, out, G, outw, fl, which, fa, st);
+    case 3: return dispatch_waves<3>(L, ws, out, G, outw, fl, which, fa, st);
+    case 4: return dispatch_waves<4>(L, ws, out, G, outw, fl, which, fa, st);
+    case 5: return dispatch_waves<5>(L, ws, out, G, outw, fl, which, fa, st);
+    case 6: return dispatch_waves<6>(L, ws, out, G, outw, fl, which, fa, st);
+    case 7: return dispatch_waves<7>(L, ws, out, G, outw, fl, which, fa, st);
+    case 8: return dispatch_waves<8>(L, ws, out, G, outw, fl, which, fa, st);
+    case 16: return dispatch_waves<16>(L, ws, out, G, outw, fl, which, fa, st);
     default: return -1;
   }
 }
 
 }  // namespace
 
-int launch_render_fwd(const Layout& L, void* ws, const rogs_surfels*, float* out, uint32_t mask,
-                      bool save, hipStream_t st) {
+int launch_render_fwd(const Layout& L, void* ws, const rogs_surfels*, float* out,
+                      const FwdArgs& fa, hipStream_t st) {
   if (L.total_tiles <= 0) return 0;
-  return dispatch(L, ws, nullptr, nullptr, out, nullptr, 0, mask, save, st);
+  return dispatch(L, ws, nullptr, nullptr, out, nullptr, 0, fa, st);
 }
 
 int launch_render_bwd(const Layout& L, void* ws, const rogs_surfels*, const float* out,
                       const float* G, hipStream_t st) {
   if (L.total_tiles <= 0) return 0;
-  return dispatch(L, ws, out, G, nullptr, nullptr, 1, 0u, false, st);
+  return dispatch(L, ws, out, G, nullptr, nullptr, 1, FwdArgs{}, st);
 }
 
 void launch_count_work(const Layout& L, void* ws, unsigned long long* counts, hipStream_t st) {
@@ -1234,7 +1237,7 @@ void launch_count_work(const Layout& L, void* ws, unsigned long long* counts, hi
 
 int launch_render_step(const Layout& L, void* ws, const FusedLoss& fl, hipStream_t st) {
   if (L.total_tiles <= 0) return 0;
-  return dispatch(L, ws, nullptr, nullptr, nullptr, &fl, 2, 0u, false, st);
+  return dispatch(L, ws, nullptr, nullptr, nullptr, &fl, 2, FwdArgs{}, st);
 }
 
 }  // namespace rogs

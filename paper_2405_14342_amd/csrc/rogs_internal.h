@@ -44,24 +44,33 @@ struct ViewDev {
   // contract's own operations: the pinhole clamp limits 0.65 W / f_x and
   // 0.65 H / f_y, and 1 / tw, 1 / th (exact: the tile sides are powers of
   // two, so multiplying by them rounds exactly as dividing by the sides)
-  double limx, limy, itw, ith;
-  // bounds for frustum_outside: the least upper bound of |dM / ds| per row,
-  // and the image size padded to whole tiles
-  double kx, ky, wpad, hpad;
-  // the view's own output (ViewOut), used by ctx_render_own
-  float* out;
-  int64_t out_plane, out_row;
-  float elev_ref;
+  double limx, limy;
+  float itw, ith;
+  float kx, ky;         // bounds of |dM / ds| per row for frustum_outside
 };
 
 // The output of one view of a served batch or an export: the planes of ch
-// (ROGS_CH_*, in the order RGB, SEM, D, A, ELEV), pixel (x, y) of plane k at
-// out[k plane + y row + x].
+// (ROGS_CH_*, in the order RGB, SEM, D, A, ELEV).  On the device ViewOutDev
+// lies in the loss partials' place (12 bytes per 256 pixels, which the loss
+// writes before it reads them), so the workspace is no larger for it.
 struct ViewOut {
   uint32_t ch;
   float* out;
-  int64_t plane, row;
   float elev_ref;
+};
+struct ViewOutDev {
+  uint32_t lo, hi;      // address of the output
+  float elev_ref;
+};
+static_assert(sizeof(ViewOutDev) == 12, "one loss partial per view holds it");
+
+// What a forward writes: the planes of mask; with save the per-pixel state of
+// the backward; pixel (x, y) of plane k of a view's own output at out[k plane +
+// y row + x], plane = 0 for images of the view's size.
+struct FwdArgs {
+  uint32_t mask = 0;
+  bool save = false;
+  int64_t plane = 0, row = 0;
 };
 
 // Number of semantic classes with a compiled kernel set.
@@ -194,10 +203,10 @@ __device__ inline bool frustum_outside(const ViewDev& c, double r, double sqrt_e
   if (!(zz > 0.0)) return false;
   const double ss = r * ((double)fabsf(sxf) + (double)fabsf(syf));
   const double pad = (r * sqrt_eps + 1.01) * zz;
-  const double fu = (double)c.fx * tx, cu = (double)c.cx * zz, wu = c.wpad * zz;
-  const double fv = (double)c.fy * ty, cv = (double)c.cy * zz, wv = c.hpad * zz;
-  const double mu = c.kx * ss + pad + 1e-12 * (fabs(fu) + fabs(cu) + wu);
-  const double mv = c.ky * ss + pad + 1e-12 * (fabs(fv) + fabs(cv) + wv);
+  const double fu = (double)c.fx * tx, cu = (double)c.cx * zz, wu = (double)(c.tiles_x * c.tw) * zz;
+  const double fv = (double)c.fy * ty, cv = (double)c.cy * zz, wv = (double)(c.tiles_y * c.th) * zz;
+  const double mu = (double)c.kx * ss + pad + 1e-12 * (fabs(fu) + fabs(cu) + wu);
+  const double mv = (double)c.ky * ss + pad + 1e-12 * (fabs(fv) + fabs(cv) + wv);
   const double pu = fu + cu, pv = fv + cv;
   return pu + mu < 0.0 || pu - mu > wu || pv + mv < 0.0 || pv - mv > wv;
 }
@@ -281,10 +290,10 @@ __device__ inline Proj project_contract(const ViewDev& c, float eps_f, float qcu
   if (!isfinite(u) || !isfinite(v) || !isfinite(hx) || !isfinite(hy) || !isfinite(A) ||
       !isfinite(B) || !isfinite(C))
     return r;
-  const int x0 = clamp_tile(floor((u - hx) * c.itw), c.tiles_x);
-  const int x1 = clamp_tile(floor((u + hx) * c.itw) + 1.0, c.tiles_x);
-  const int y0 = clamp_tile(floor((v - hy) * c.ith), c.tiles_y);
-  const int y1 = clamp_tile(floor((v + hy) * c.ith) + 1.0, c.tiles_y);
+  const int x0 = clamp_tile(floor((u - hx) * (double)c.itw), c.tiles_x);
+  const int x1 = clamp_tile(floor((u + hx) * (double)c.itw) + 1.0, c.tiles_x);
+  const int y0 = clamp_tile(floor((v - hy) * (double)c.ith), c.tiles_y);
+  const int y1 = clamp_tile(floor((v + hy) * (double)c.ith) + 1.0, c.tiles_y);
   if (x0 >= x1 || y0 >= y1) return r;
   r.vis = true;
   r.uh = (float)u;
@@ -770,20 +779,18 @@ void launch_layout_mask(const rogs_pose* poses, int np, double x0, double y0, fl
 void launch_layout_fill(const rogs_pose* poses, int np, double x0, double y0, float h, int W,
                         int H, void* scratch, int64_t n, int32_t* idx, float* x, float* y,
                         float* z, float* q, int32_t* nbr, hipStream_t st);
-int launch_render_fwd(const Layout& L, void* ws, const rogs_surfels* s, float* out, uint32_t mask,
-                      bool save, hipStream_t st);
+int launch_render_fwd(const Layout& L, void* ws, const rogs_surfels* s, float* out,
+                      const FwdArgs& fa, hipStream_t st);
 // Waits for the fused steps in flight and forgets them and the captured
 // graph: the next rogs_step_fused starts afresh and rogs_fused_status reports
 // no step until then.
 void ctx_fused_forget(rogs_ctx* c);
 // rogs_project of views with outputs of their own (one ViewOut per view), and
 // the forward that writes them: of each view the planes of its ch and mask.
-// save keeps the per-pixel state that rogs_render_bwd needs.
 int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
                     const rogs_render_opts* opts, void* ws, size_t ws_bytes,
                     int64_t pair_capacity, void* stream, const ViewOut* outs);
-int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, uint32_t mask, bool save,
-                   void* stream);
+int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, const FwdArgs& fa, void* stream);
 void launch_loss(const Layout& L, void* ws, const float* out, const rogs_targets* t, float* G,
                  float* loss_out, float* d_exp, hipStream_t st);
 int launch_render_bwd(const Layout& L, void* ws, const rogs_surfels* s, const float* out,

@@ -137,12 +137,11 @@ bool run_batch(rogs_server* s, ServeLane& ln, std::vector<Item>& batch) {
   // each view composites only the planes its request asked for, into its buffer
   std::vector<rogs::ViewOut> outs;
   for (const Item& it : batch)
-    outs.push_back({it.req.channels, it.req.out, (int64_t)it.req.cam.w * it.req.cam.h,
-                    it.req.cam.w, it.req.elev_ref});
+    outs.push_back({it.req.channels, it.req.out, it.req.elev_ref});
   int r = rogs::ctx_project_own(ln.ctx, &s->map, cams.data(), (int)cams.size(), &s->opts, ws, wsb,
                                 cap, ln.st, outs.data());
   if (r == ROGS_OK) r = rogs_bin_sort(ln.ctx, ws, nullptr, 0u, ln.st);
-  if (r == ROGS_OK) r = rogs::ctx_render_own(ln.ctx, &s->map, ws, ROGS_CH_ALL, false, ln.st);
+  if (r == ROGS_OK) r = rogs::ctx_render_own(ln.ctx, &s->map, ws, {(uint32_t)ROGS_CH_ALL}, ln.st);
   if (r == ROGS_OK && hipGetLastError() != hipSuccess) r = ROGS_EHIP;
   int64_t n = 0;
   int32_t ovf = 0;
