@@ -333,8 +333,8 @@ int upload_views(rogs_ctx* c, const Layout& L, const rogs_camera* cams, void* ws
     c->stage_bytes = need;
   }
   fill_view_table(L, cams, c->stage, outs);
-  hipError_t e = hipMemcpyAsync(rogs::at<void>(ws, L.o_views), c->stage, vbytes + fbytes,
-                                hipMemcpyHostToDevice, st);
+  rogs::launch_upload(L, ws, c->stage, vbytes + fbytes, st);
+  hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipEventRecord(c->stage_evt, st);
   if (e != hipSuccess) return hip_fail(c, e, "view table upload");
   c->stage_pending = true;
@@ -567,7 +567,9 @@ int rogs_pair_count(rogs_ctx* c, void* ws, int64_t* n_pairs, int32_t* overflow, 
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(c, e, "rogs_pair_count");
   if (n_pairs) *n_pairs = (int64_t)c->readback[rogs::kMiscPairs];
-  if (overflow) *overflow = (int32_t)c->readback[rogs::kMiscOverflow];
+  if (overflow)
+    *overflow = (int64_t)c->readback[rogs::kMiscPairs] > c->L.cap ||
+                (int64_t)c->readback[rogs::kMiscVisible] > c->L.scap;
   c->last_visible = (int64_t)c->readback[rogs::kMiscVisible];
   return ROGS_OK;
 }
@@ -911,10 +913,6 @@ int fused_sequence(rogs_ctx* c, Layout& L, const rogs_train_state* t, const rogs
   prof_end(c, st);
   if (r != 0) return fail(c, ROGS_EINVAL, "unsupported n_sem / tile shape");
   rogs::AdamArgs aa = fused_adam_args(o, L, ws, t->step_state);
-  prof_begin(c, 6, st);
-  // per-view loss sums, dL/d(a, b) and the exposure's Adam step
-  rogs::launch_loss_tiles(L, ws, t->d_exposure, t->exposure, t->m_exp, t->v_exp, aa, st);
-  prof_end(c, st);
   prof_begin(c, 8, st);
   // grid-side terms (Eq. 10, 11) from the heights before the update
   const bool reg = tg->nbr || tg->zbar;
@@ -922,7 +920,8 @@ int fused_sequence(rogs_ctx* c, Layout& L, const rogs_train_state* t, const rogs
     rogs::launch_elev_reg(L.N, t->params, tg->nbr, tg->lambda_smooth, tg->zbar, tg->lambda_z,
                           rogs::at<float>(ws, L.o_dzr), nullptr, rogs::at<float>(ws, L.o_regpart),
                           rogs::at<float>(ws, L.o_regtot), false, st);
-  rogs::launch_slot_sums(L, ws, st, false);      // misc's long-slot count is still zero
+  // with the per-view loss sums, dL/d(a, b) and the exposure's Adam step
+  rogs::launch_slot_loss_sums(L, ws, t->d_exposure, t->exposure, t->m_exp, t->v_exp, aa, st);
   rogs::launch_proj_bwd_adam(L, ws, t->x, t->y, t->params, t->m, t->v, t->s_act, t->alpha_act,
                              t->grads, aa, nullptr, nullptr, nullptr, nullptr,
                              reg ? rogs::at<const float>(ws, L.o_dzr) : nullptr, st);

@@ -298,6 +298,102 @@ __device__ __forceinline__ void adam_surfel(int i, size_t N, float* __restrict__
   a_act[i] = 1.0f / (1.0f + expf(-P[7 * N + i]));
 }
 
+// Adam on a plain array (the per-view exposure (a, b)).  With a step state
+// the step comes from the device and an overflow skips the update.
+__device__ __forceinline__ void adam_plain_elem(int i, float g, float* __restrict__ P,
+                                                float* __restrict__ M, float* __restrict__ Vv,
+                                                const AdamArgs& aa) {
+  if (aa.misc && aa.misc[kMiscOverflow]) return;
+  const int64_t step = aa.state ? aa.state->step + 1 : aa.step;
+  float bc1, bc2s;
+  adam_bias(aa.b1, aa.b2, step, bc1, bc2s);
+  const float m = aa.b1 * M[i] + (1.0f - aa.b1) * g;
+  const float v = aa.b2 * Vv[i] + (1.0f - aa.b2) * g * g;
+  M[i] = m;
+  Vv[i] = v;
+  P[i] -= (aa.lr.exposure / bc1) * (m / (sqrtf(v) / bc2s + aa.eps));
+}
+
+// Per-view sums of the fused step's per-tile partials (loss, dL/da, dL/db)
+// in two fixed-order stages: block (c, v) adds tiles c * kTileChunk ... of
+// view v (8 per thread, then a fixed tree), and one wave per view adds the
+// chunks in order (lane-strided, then a fixed tree), overwrites dL/d(a, b)
+// and applies Adam to the view's exposure (a, b).  The result does not
+// depend on scheduling.  They have blocks of their own at the front of the two
+// slot-sum launches (launches of their own took 4.5 us each).
+constexpr int kTileChunk = 8 * 256;
+
+__device__ __forceinline__ void loss_tiles_block(const ViewDev* __restrict__ views, int V,
+                                                 int64_t total_tiles,
+                                                 const float* __restrict__ part, int nchunk,
+                                                 float* __restrict__ cpart, int c, int v) {
+  __shared__ float s[3][256];
+  const int64_t t0 = views[v].tile_off;
+  const int64_t t1 = (v + 1 < V) ? views[v + 1].tile_off : total_tiles;
+  const int64_t k0 = t0 + (int64_t)c * kTileChunk;
+  float l = 0.0f, a = 0.0f, b = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int64_t k = k0 + threadIdx.x + 256 * i;
+    if (k < t1) {
+      l += part[3 * k];
+      a += part[3 * k + 1];
+      b += part[3 * k + 2];
+    }
+  }
+  s[0][threadIdx.x] = l;
+  s[1][threadIdx.x] = a;
+  s[2][threadIdx.x] = b;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) {
+      s[0][threadIdx.x] += s[0][threadIdx.x + w];
+      s[1][threadIdx.x] += s[1][threadIdx.x + w];
+      s[2][threadIdx.x] += s[2][threadIdx.x + w];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < 3) cpart[((size_t)v * nchunk + c) * 3 + threadIdx.x] = s[threadIdx.x][0];
+}
+
+__device__ __forceinline__ void loss_chunks_wave(const float* __restrict__ cpart, int nchunk,
+                                                 float* __restrict__ per_view,
+                                                 float* __restrict__ d_exp,
+                                                 float* __restrict__ expo,
+                                                 float* __restrict__ m_exp,
+                                                 float* __restrict__ v_exp, const AdamArgs& aa,
+                                                 int v) {
+  const int lane = threadIdx.x;
+  float l = 0.0f, a = 0.0f, b = 0.0f;
+  for (int c = lane; c < nchunk; c += 64) {
+    const float* q = cpart + ((size_t)v * nchunk + c) * 3;
+    l += q[0];
+    a += q[1];
+    b += q[2];
+  }
+  l = wave_sum_f(l);
+  a = wave_sum_f(a);
+  b = wave_sum_f(b);
+  if (lane == 0) {
+    per_view[v] = l;
+    if (d_exp) {
+      d_exp[2 * v] = a;
+      d_exp[2 * v + 1] = b;
+    }
+  }
+  if (expo && lane < 2) adam_plain_elem(2 * v + lane, lane == 0 ? a : b, expo, m_exp, v_exp, aa);
+}
+
+// The fused step's loss sums beside the slot sums: blocks is the count of
+// k_slot_sums' blocks that add tile partials, 0 for none.
+struct LossSums {
+  int blocks = 0, nchunk = 0;
+  const float* part = nullptr;
+  float *cpart = nullptr, *per_view = nullptr;
+  float *d_exp = nullptr, *expo = nullptr, *m_exp = nullptr, *v_exp = nullptr;
+  AdamArgs aa{};
+};
+
 // Per-slot sums of the per-pair gradient records.  The records of a visible
 // slot are contiguous in emission order; a slot with at most kLongRows records
 // is summed in record order by Q threads, one per float4 column of the record
@@ -315,11 +411,19 @@ __global__ __launch_bounds__(256) void k_slot_sums(const uint32_t* __restrict__ 
                                                    const float* __restrict__ gpair,
                                                    float* __restrict__ ssum,
                                                    uint32_t* __restrict__ long_list,
-                                                   uint32_t* __restrict__ long_count) {
+                                                   uint32_t* __restrict__ long_count,
+                                                   const ViewDev* __restrict__ views, int V,
+                                                   int64_t total_tiles, LossSums ls) {
   constexpr int GSC = ((10 + C) + 3) & ~3;
   constexpr int Q = GSC / 4;
+  if ((int)blockIdx.x < ls.blocks) {
+    const int v = (int)blockIdx.x / ls.nchunk;
+    loss_tiles_block(views, V, total_tiles, ls.part, ls.nchunk, ls.cpart,
+                     (int)blockIdx.x - v * ls.nchunk, v);
+    return;
+  }
   const int64_t S = min((int64_t)misc[kMiscVisible], scap);
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = (int64_t)((int)blockIdx.x - ls.blocks) * 256 + threadIdx.x;
   const int64_t k = t / Q;
   const int q = (int)(t - k * Q);
   if (k >= S) return;
@@ -356,14 +460,20 @@ __global__ __launch_bounds__(64) void k_slot_sums_long(const uint32_t* __restric
                                                        const uint32_t* __restrict__ scnt,
                                                        const uint32_t* __restrict__ soff,
                                                        const float* __restrict__ gpair,
-                                                       float* __restrict__ ssum) {
+                                                       float* __restrict__ ssum, int nv,
+                                                       LossSums ls) {
   constexpr int NV = 10 + C;
   constexpr int GSC = ((10 + C) + 3) & ~3;
   const int lane = threadIdx.x;
+  if ((int)blockIdx.x < nv) {
+    loss_chunks_wave(ls.cpart, ls.nchunk, ls.per_view, ls.d_exp, ls.expo, ls.m_exp, ls.v_exp,
+                     ls.aa, (int)blockIdx.x);
+    return;
+  }
   const uint32_t nl = *long_count;
   const int my_comp = rs_comp(lane, NV);
   const bool writer = my_comp >= 0 && (lane & rs_dup_bits(NV)) == 0;
-  for (uint32_t it = blockIdx.x; it < nl; it += gridDim.x) {
+  for (uint32_t it = blockIdx.x - nv; it < nl; it += gridDim.x - nv) {
     const uint32_t k = long_list[it];
     const uint32_t n = scnt[k], o = soff[k];
     const uint32_t m = ((int64_t)o + n <= cap) ? n : (((int64_t)o < cap) ? (uint32_t)(cap - o) : 0u);
@@ -619,96 +729,11 @@ __global__ __launch_bounds__(256) void k_adam(int N, float* __restrict__ P,
                  aa.eps, bc1, bc2s);
 }
 
-// Adam on a plain array (the per-view exposure (a, b)).  With a step state
-// the step comes from the device and an overflow skips the update.
-__device__ __forceinline__ void adam_plain_elem(int i, float g, float* __restrict__ P,
-                                                float* __restrict__ M, float* __restrict__ Vv,
-                                                const AdamArgs& aa) {
-  if (aa.misc && aa.misc[kMiscOverflow]) return;
-  const int64_t step = aa.state ? aa.state->step + 1 : aa.step;
-  float bc1, bc2s;
-  adam_bias(aa.b1, aa.b2, step, bc1, bc2s);
-  const float m = aa.b1 * M[i] + (1.0f - aa.b1) * g;
-  const float v = aa.b2 * Vv[i] + (1.0f - aa.b2) * g * g;
-  M[i] = m;
-  Vv[i] = v;
-  P[i] -= (aa.lr.exposure / bc1) * (m / (sqrtf(v) / bc2s + aa.eps));
-}
-
 __global__ void k_adam_plain(int n, float* __restrict__ P, const float* __restrict__ Gd,
                              float* __restrict__ M, float* __restrict__ Vv, AdamArgs aa) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   adam_plain_elem(i, Gd[i], P, M, Vv, aa);
-}
-
-// Per-view sums of the fused step's per-tile partials (loss, dL/da, dL/db)
-// in two fixed-order stages: block (c, v) adds tiles c * kTileChunk ... of
-// view v (8 per thread, then a fixed tree), and one wave per view adds the
-// chunks in order (lane-strided, then a fixed tree), overwrites dL/d(a, b)
-// and applies Adam to the view's exposure (a, b).  The result does not
-// depend on scheduling.
-constexpr int kTileChunk = 8 * 256;
-
-__global__ __launch_bounds__(256) void k_loss_tiles(const ViewDev* __restrict__ views, int V,
-                                                    int64_t total_tiles,
-                                                    const float* __restrict__ part, int nchunk,
-                                                    float* __restrict__ cpart) {
-  __shared__ float s[3][256];
-  const int v = blockIdx.y, c = blockIdx.x;
-  const int64_t t0 = views[v].tile_off;
-  const int64_t t1 = (v + 1 < V) ? views[v + 1].tile_off : total_tiles;
-  const int64_t k0 = t0 + (int64_t)c * kTileChunk;
-  float l = 0.0f, a = 0.0f, b = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int64_t k = k0 + threadIdx.x + 256 * i;
-    if (k < t1) {
-      l += part[3 * k];
-      a += part[3 * k + 1];
-      b += part[3 * k + 2];
-    }
-  }
-  s[0][threadIdx.x] = l;
-  s[1][threadIdx.x] = a;
-  s[2][threadIdx.x] = b;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      s[0][threadIdx.x] += s[0][threadIdx.x + w];
-      s[1][threadIdx.x] += s[1][threadIdx.x + w];
-      s[2][threadIdx.x] += s[2][threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 3) cpart[((size_t)v * nchunk + c) * 3 + threadIdx.x] = s[threadIdx.x][0];
-}
-
-__global__ __launch_bounds__(64) void k_loss_chunks(const float* __restrict__ cpart, int nchunk,
-                                                    float* __restrict__ per_view,
-                                                    float* __restrict__ d_exp,
-                                                    float* __restrict__ expo,
-                                                    float* __restrict__ m_exp,
-                                                    float* __restrict__ v_exp, AdamArgs aa) {
-  const int v = blockIdx.x, lane = threadIdx.x;
-  float l = 0.0f, a = 0.0f, b = 0.0f;
-  for (int c = lane; c < nchunk; c += 64) {
-    const float* q = cpart + ((size_t)v * nchunk + c) * 3;
-    l += q[0];
-    a += q[1];
-    b += q[2];
-  }
-  l = wave_sum_f(l);
-  a = wave_sum_f(a);
-  b = wave_sum_f(b);
-  if (lane == 0) {
-    per_view[v] = l;
-    if (d_exp) {
-      d_exp[2 * v] = a;
-      d_exp[2 * v + 1] = b;
-    }
-  }
-  if (expo && lane < 2) adam_plain_elem(2 * v + lane, lane == 0 ? a : b, expo, m_exp, v_exp, aa);
 }
 
 // Closes a fused step: counts it (or its skip on overflow) and keeps its loss;
@@ -843,38 +868,46 @@ void launch_proj_bwd_adam(const Layout& L, void* ws, const float* x, const float
 
 namespace {
 template <int C>
-void slot_sums_launch(const Layout& L, void* ws, hipStream_t st, bool clear) {
+void slot_sums_launch(const Layout& L, void* ws, hipStream_t st, bool clear, const LossSums& ls) {
   uint32_t* misc = at<uint32_t>(ws, L.o_misc);
   const int64_t s_grid = L.scap;
-  if (s_grid <= 0) return;
+  const int nv = ls.blocks ? L.V : 0;
+  if (s_grid <= 0 && !ls.blocks) return;
   if (clear) fill_u32(misc + kMiscLong, 0u, 1, st);
   constexpr int Q = (((10 + C) + 3) & ~3) / 4;
-  hipLaunchKernelGGL((k_slot_sums<C>), dim3((unsigned)((s_grid * Q + 255) / 256)), dim3(256), 0, st,
+  hipLaunchKernelGGL((k_slot_sums<C>), dim3((unsigned)((s_grid * Q + 255) / 256 + ls.blocks)),
+                     dim3(256), 0, st,
                      misc, L.scap, L.cap, at<const uint32_t>(ws, L.o_scnt),
                      at<const uint32_t>(ws, L.o_soff), at<const float>(ws, L.o_gpair),
-                     at<float>(ws, L.o_ssum), at<uint32_t>(ws, L.o_long), misc + kMiscLong);
-  hipLaunchKernelGGL((k_slot_sums_long<C>), dim3(16384), dim3(64), 0, st,
+                     at<float>(ws, L.o_ssum), at<uint32_t>(ws, L.o_long), misc + kMiscLong,
+                     at<const ViewDev>(ws, L.o_views), L.V, L.total_tiles, ls);
+  hipLaunchKernelGGL((k_slot_sums_long<C>), dim3(16384 + nv), dim3(64), 0, st,
                      at<const uint32_t>(ws, L.o_long), misc + kMiscLong, L.cap,
                      at<const uint32_t>(ws, L.o_scnt), at<const uint32_t>(ws, L.o_soff),
-                     at<const float>(ws, L.o_gpair), at<float>(ws, L.o_ssum));
+                     at<const float>(ws, L.o_gpair), at<float>(ws, L.o_ssum), nv, ls);
 }
 }  // namespace
 
-void launch_slot_sums(const Layout& L, void* ws, hipStream_t st, bool clear) {
-  ROGS_SEM_SWITCH(L.C, (slot_sums_launch<KC>(L, ws, st, clear)));
+void launch_slot_sums(const Layout& L, void* ws, hipStream_t st) {
+  ROGS_SEM_SWITCH(L.C, (slot_sums_launch<KC>(L, ws, st, true, LossSums{})));
 }
 
-void launch_loss_tiles(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
-                       float* v_exp, const AdamArgs& aa, hipStream_t st) {
-  float* per_view = reinterpret_cast<float*>(at<uint32_t>(ws, L.o_mcount) + L.V);
+void launch_slot_loss_sums(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
+                           float* v_exp, const AdamArgs& aa, hipStream_t st) {
+  LossSums ls;
+  ls.nchunk = (int)((L.max_view_tiles + kTileChunk - 1) / kTileChunk);
+  ls.blocks = ls.nchunk * L.V;
+  ls.part = at<const float>(ws, L.o_tpart);
   // the plain loss's block partials are unused on the fused path: chunk sums go there
-  float* cpart = at<float>(ws, L.o_lpart) + 2 * (L.V + 1);
-  const int nchunk = (int)((L.max_view_tiles + kTileChunk - 1) / kTileChunk);
-  hipLaunchKernelGGL(k_loss_tiles, dim3((unsigned)nchunk, (unsigned)L.V), dim3(256), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.total_tiles,
-                     at<const float>(ws, L.o_tpart), nchunk, cpart);
-  hipLaunchKernelGGL(k_loss_chunks, dim3((unsigned)L.V), dim3(64), 0, st, cpart, nchunk, per_view,
-                     d_exp, expo, m_exp, v_exp, aa);
+  ls.cpart = at<float>(ws, L.o_lpart) + 2 * (L.V + 1);
+  ls.per_view = reinterpret_cast<float*>(at<uint32_t>(ws, L.o_mcount) + L.V);
+  ls.d_exp = d_exp;
+  ls.expo = expo;
+  ls.m_exp = m_exp;
+  ls.v_exp = v_exp;
+  ls.aa = aa;
+  // (the step's counters start at zero: no clear of the long-slot count)
+  ROGS_SEM_SWITCH(L.C, (slot_sums_launch<KC>(L, ws, st, false, ls)));
 }
 
 void launch_mask_count(const Layout& L, void* ws, const uint8_t* mask, hipStream_t st) {

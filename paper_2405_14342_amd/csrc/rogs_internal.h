@@ -118,31 +118,10 @@ inline int mask_chunks(const Layout& L) {
 // the slots that fit the slot capacity)
 enum MiscSlot {
   kMiscPairs = 0, kMiscOverflow = 1, kMiscVisible = 2, kMiscLong = 3, kMiscEmit = 4,
-  kMiscTicketScan = 5,   // last-block ticket of the count-table scan
   kMiscList = 6,         // (range, view) blocks left by the projection's cull
   kMiscWork = 8,   // two 64-bit work counters (words 8-11)
   kMiscCount = 16
 };
-
-// Last-block election for a grid-wide tail: each block calls it once, after
-// writing its partial results, from every thread; it returns true in exactly
-// one block, the last to arrive, which then sees every block's writes.  The
-// ticket word must be zero before the launch and is zero again afterwards.
-__device__ __forceinline__ bool last_block(uint32_t* ticket) {
-  __shared__ uint32_t s_last;
-  __threadfence();                     // this block's results, visible device-wide
-  __syncthreads();
-  if (threadIdx.x == 0 && threadIdx.y == 0) {
-    const uint32_t n = gridDim.x * gridDim.y;
-    const uint32_t t = atomicAdd(ticket, 1u);
-    s_last = (t == n - 1u) ? 1u : 0u;
-    if (t == n - 1u) atomicExch(ticket, 0u);
-  }
-  __syncthreads();
-  const bool last = s_last != 0u;
-  if (last) __threadfence();           // acquire the other blocks' results
-  return last;
-}
 
 int make_layout(const rogs_surfels* s, const rogs_camera* cams, int n_views,
                 const rogs_render_opts* opts, int64_t cap, int64_t scap, Layout* L,
@@ -748,6 +727,9 @@ struct AdamArgs {
 
 // ------------------------------------------------------------------ launchers
 
+// Copies the view table (bytes of pinned host memory) into the workspace and
+// clears the batch's counters.
+void launch_upload(const Layout& L, void* ws, const void* stage, size_t bytes, hipStream_t st);
 void launch_project(const Layout& L, void* ws, const rogs_surfels* s, hipStream_t st,
                     const uint8_t* mask = nullptr);
 // Feature records of the surfels that some view sees; after launch_project and
@@ -796,11 +778,9 @@ void launch_loss(const Layout& L, void* ws, const float* out, const rogs_targets
 int launch_render_bwd(const Layout& L, void* ws, const rogs_surfels* s, const float* out,
                       const float* G, hipStream_t st);
 int launch_render_step(const Layout& L, void* ws, const FusedLoss& fl, hipStream_t st);
-// Per-slot sums of the per-pair gradient records (before the projection adjoint).
-// Sums each visible slot's per-pair gradient records.  clear = reset the
-// long-slot count first (false only where the projection's counter reset is
-// known to be the last write to it).
-void launch_slot_sums(const Layout& L, void* ws, hipStream_t st, bool clear = true);
+// Sums each visible slot's per-pair gradient records (before the projection
+// adjoint).
+void launch_slot_sums(const Layout& L, void* ws, hipStream_t st);
 void launch_proj_bwd(const Layout& L, void* ws, const rogs_surfels* s, float* grads,
                      bool accumulate, hipStream_t st);
 void launch_adam(int n, int C, float* params, const float* grads, float* m, float* v,
@@ -815,8 +795,10 @@ void launch_proj_bwd_adam(const Layout& L, void* ws, const float* x, const float
                           const AdamArgs& aa, float* expo, const float* dexpo, float* me,
                           float* ve, const float* dzr, hipStream_t st);
 // Fused: per-view loss and dL/d(a, b) (overwritten) from the per-tile partials.
-void launch_loss_tiles(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
-                       float* v_exp, const AdamArgs& aa, hipStream_t st);
+// The fused step's slot sums, with its per-view loss sums, dL/d(a, b) and the
+// exposure's Adam step beside them.
+void launch_slot_loss_sums(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
+                           float* v_exp, const AdamArgs& aa, hipStream_t st);
 void launch_mask_count(const Layout& L, void* ws, const uint8_t* mask, hipStream_t st);
 void launch_step_end(const Layout& L, void* ws, StepState* state, const AdamArgs& aa,
                      const float* reg_total, hipStream_t st);
