@@ -73,3 +73,19 @@ def test_overflow_is_known_before_binning():
         st.rg.project(surf, st.cams, st.opts, ws, cap)
         n, overflow = st.rg.pair_count(ws)
         assert bool(overflow) == full and n > 64
+
+
+@pytest.mark.parametrize("chunk", [64, 40, 128])
+def test_export_restarts_after_an_overflow(chunk):
+    """Chunk counts are read a few chunks at a time: an export that overflows
+    and is repeated with the capacity it reports gives the same bits and the
+    same largest count as one with room from the start."""
+    st = _state(3000, 64, 64)
+    args = (-0.9, -0.6, 180, 120, 0.01, chunk, 10.0, B.CH_RGB | B.CH_A | B.CH_ELEV)
+    out = [torch.zeros((5, 120, 180), device="cuda") for _ in range(2)]
+    n0 = st.rg.bev_export(st.surfels(), st.opts, *args, out[0])
+    n1 = st.rg.bev_export(st.surfels(), st.opts, *args, out[1], pair_capacity=16)
+    torch.cuda.synchronize()
+    assert n0 == n1 > 16
+    assert float(out[0][3].max()) > 0.3
+    assert torch.equal(out[0].nan_to_num(-1.0), out[1].nan_to_num(-1.0))
