@@ -1,5 +1,6 @@
 """Build librogs.so (hand-written HIP for gfx950) in-tree with hipcc, and the
-serving runtime's host-sanitizer test driver."""
+test drivers: the serving runtime's under host sanitizers and the workspace
+layout's host checks."""
 from __future__ import annotations
 
 import os
@@ -29,6 +30,10 @@ SAN_DRIVER = os.path.join(ROOT, "tests", "serve_sanitize_driver.cpp")
 SAN_EXE = os.path.join(ROOT, "tests", "_bin", "serve_sanitize")
 SAN_FLAGS = ("-Xarch_host -fsanitize=address -Xarch_host -fsanitize=undefined "
              "-Xarch_host -fno-sanitize-recover=all -Xarch_host -fno-omit-frame-pointer").split()
+
+# Host-only checks of the workspace layout, linked with the library's objects.
+LAYOUT_DRIVER = os.path.join(ROOT, "tests", "layout_driver.cpp")
+LAYOUT_EXE = os.path.join(ROOT, "tests", "_bin", "layout_checks")
 
 
 def _jobs() -> int:
@@ -64,6 +69,22 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_layout_checks(verbose: bool = False) -> str:
+    """The layout's host checks (tests/layout_driver.cpp), linked with the
+    objects that build() left."""
+    objs = [os.path.join(OBJ, "lib", os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    os.makedirs(os.path.dirname(LAYOUT_EXE), exist_ok=True)
+    drv = os.path.join(OBJ, "lib", "layout_driver.o")
+    tmp = LAYOUT_EXE + ".tmp"
+    for cmd in ([HIPCC] + FLAGS + ["-x", "hip", "-c", LAYOUT_DRIVER, "-o", drv],
+                [HIPCC, "--offload-arch=gfx950", drv] + objs + ["-lpthread", "-o", tmp]):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+    os.replace(tmp, LAYOUT_EXE)
+    return LAYOUT_EXE
+
+
 def build_serve_sanitizer(verbose: bool = False) -> str:
     """The serving-runtime test driver (tests/serve_sanitize_driver.cpp)
     linked with the library sources, host code built with ASan and UBSan."""
@@ -86,6 +107,7 @@ def build_serve_sanitizer(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     build(verbose="-v" in sys.argv)
+    build_layout_checks(verbose="-v" in sys.argv)
     print(LIB)
     if "--sanitizer" in sys.argv:
         print(build_serve_sanitizer(verbose="-v" in sys.argv))

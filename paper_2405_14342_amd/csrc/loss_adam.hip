@@ -317,20 +317,29 @@ __device__ __forceinline__ void adam_plain_elem(int i, float g, float* __restric
 // Per-view sums of the fused step's per-tile partials (loss, dL/da, dL/db)
 // in two fixed-order stages: block (c, v) adds tiles c * kTileChunk ... of
 // view v (8 per thread, then a fixed tree), and one wave per view adds the
-// chunks in order (lane-strided, then a fixed tree), overwrites dL/d(a, b)
-// and applies Adam to the view's exposure (a, b).  The result does not
+// view's chunks in order (lane-strided, then a fixed tree), overwrites dL/d(a,
+// b) and applies Adam to the view's exposure (a, b).  The result does not
 // depend on scheduling.  They have blocks of their own at the front of the two
-// slot-sum launches (launches of their own took 4.5 us each).
-constexpr int kTileChunk = 8 * 256;
+// slot-sum launches (launches of their own took 4.5 us each).  The chunk sums
+// lie in the plain loss's block partials, each view's in its own blocks' place
+// (loss_chunk_at).
+static_assert(kTileChunk == 8 * 256, "8 tiles per thread");
+
+__device__ __forceinline__ int64_t view_tiles(const ViewDev* __restrict__ views, int V,
+                                              int64_t total_tiles, int v) {
+  return ((v + 1 < V) ? views[v + 1].tile_off : total_tiles) - views[v].tile_off;
+}
 
 __device__ __forceinline__ void loss_tiles_block(const ViewDev* __restrict__ views, int V,
                                                  int64_t total_tiles,
-                                                 const float* __restrict__ part, int nchunk,
+                                                 const float* __restrict__ part,
+                                                 const int64_t* __restrict__ first_blk,
                                                  float* __restrict__ cpart, int c, int v) {
   __shared__ float s[3][256];
-  const int64_t t0 = views[v].tile_off;
-  const int64_t t1 = (v + 1 < V) ? views[v + 1].tile_off : total_tiles;
-  const int64_t k0 = t0 + (int64_t)c * kTileChunk;
+  const int64_t nt = view_tiles(views, V, total_tiles, v);
+  if (c >= tile_chunks(nt)) return;        // (the launch counts the largest view's chunks)
+  const int64_t t1 = views[v].tile_off + nt;
+  const int64_t k0 = views[v].tile_off + (int64_t)c * kTileChunk;
   float l = 0.0f, a = 0.0f, b = 0.0f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -353,10 +362,11 @@ __device__ __forceinline__ void loss_tiles_block(const ViewDev* __restrict__ vie
     }
     __syncthreads();
   }
-  if (threadIdx.x < 3) cpart[((size_t)v * nchunk + c) * 3 + threadIdx.x] = s[threadIdx.x][0];
+  if (threadIdx.x < 3) cpart[loss_chunk_at(first_blk, v, c) + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__device__ __forceinline__ void loss_chunks_wave(const float* __restrict__ cpart, int nchunk,
+__device__ __forceinline__ void loss_chunks_wave(const float* __restrict__ cpart,
+                                                 const int64_t* __restrict__ first_blk, int nchunk,
                                                  float* __restrict__ per_view,
                                                  float* __restrict__ d_exp,
                                                  float* __restrict__ expo,
@@ -366,7 +376,7 @@ __device__ __forceinline__ void loss_chunks_wave(const float* __restrict__ cpart
   const int lane = threadIdx.x;
   float l = 0.0f, a = 0.0f, b = 0.0f;
   for (int c = lane; c < nchunk; c += 64) {
-    const float* q = cpart + ((size_t)v * nchunk + c) * 3;
+    const float* q = cpart + loss_chunk_at(first_blk, v, c);
     l += q[0];
     a += q[1];
     b += q[2];
@@ -387,8 +397,9 @@ __device__ __forceinline__ void loss_chunks_wave(const float* __restrict__ cpart
 // The fused step's loss sums beside the slot sums: blocks is the count of
 // k_slot_sums' blocks that add tile partials, 0 for none.
 struct LossSums {
-  int blocks = 0, nchunk = 0;
+  int blocks = 0, nchunk = 0;         // nchunk: of the largest view
   const float* part = nullptr;
+  const int64_t* first_blk = nullptr;
   float *cpart = nullptr, *per_view = nullptr;
   float *d_exp = nullptr, *expo = nullptr, *m_exp = nullptr, *v_exp = nullptr;
   AdamArgs aa{};
@@ -423,7 +434,7 @@ __global__ __launch_bounds__(256) void k_slot_sums(const uint32_t* __restrict__ 
   constexpr int Q = GSC / 4;
   if ((int)blockIdx.x < ls.blocks) {
     const int v = (int)blockIdx.x / ls.nchunk;
-    loss_tiles_block(views, V, total_tiles, ls.part, ls.nchunk, ls.cpart,
+    loss_tiles_block(views, V, total_tiles, ls.part, ls.first_blk, ls.cpart,
                      (int)blockIdx.x - v * ls.nchunk, v);
     return;
   }
@@ -467,14 +478,17 @@ __global__ __launch_bounds__(64) void k_slot_sums_long(const uint32_t* __restric
                                                        const uint32_t* __restrict__ scnt,
                                                        const uint32_t* __restrict__ soff,
                                                        const float* __restrict__ gpair,
-                                                       float* __restrict__ ssum, int nv,
-                                                       LossSums ls) {
+                                                       float* __restrict__ ssum,
+                                                       const ViewDev* __restrict__ views, int nv,
+                                                       int64_t total_tiles, LossSums ls) {
   constexpr int NV = 10 + C;
   constexpr int GSC = ((10 + C) + 3) & ~3;
   const int lane = threadIdx.x;
   if ((int)blockIdx.x < nv) {
-    loss_chunks_wave(ls.cpart, ls.nchunk, ls.per_view, ls.d_exp, ls.expo, ls.m_exp, ls.v_exp,
-                     ls.aa, (int)blockIdx.x);
+    const int v = (int)blockIdx.x;
+    loss_chunks_wave(ls.cpart, ls.first_blk,
+                     (int)tile_chunks(view_tiles(views, nv, total_tiles, v)), ls.per_view, ls.d_exp,
+                     ls.expo, ls.m_exp, ls.v_exp, ls.aa, v);
     return;
   }
   const uint32_t nl = *long_count;
@@ -891,7 +905,8 @@ void slot_sums_launch(const Layout& L, void* ws, hipStream_t st, bool clear, con
   hipLaunchKernelGGL((k_slot_sums_long<C>), dim3(16384 + nv), dim3(64), 0, st,
                      at<const uint32_t>(ws, L.o_long), misc + kMiscLong, L.cap,
                      at<const uint32_t>(ws, L.o_scnt), at<const uint32_t>(ws, L.o_soff),
-                     at<const float>(ws, L.o_gpair), at<float>(ws, L.o_ssum), nv, ls);
+                     at<const float>(ws, L.o_gpair), at<float>(ws, L.o_ssum),
+                     at<const ViewDev>(ws, L.o_views), nv, L.total_tiles, ls);
 }
 }  // namespace
 
@@ -902,10 +917,11 @@ void launch_slot_sums(const Layout& L, void* ws, hipStream_t st) {
 void launch_slot_loss_sums(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
                            float* v_exp, const AdamArgs& aa, hipStream_t st) {
   LossSums ls;
-  ls.nchunk = (int)((L.max_view_tiles + kTileChunk - 1) / kTileChunk);
+  ls.nchunk = (int)tile_chunks(L.max_view_tiles);
   ls.blocks = ls.nchunk * L.V;
   ls.part = at<const float>(ws, L.o_tpart);
   // the plain loss's block partials are unused on the fused path: chunk sums go there
+  ls.first_blk = at<const int64_t>(ws, L.o_lpart);
   ls.cpart = at<float>(ws, L.o_lpart) + 2 * (L.V + 1);
   ls.per_view = reinterpret_cast<float*>(at<uint32_t>(ws, L.o_mcount) + L.V);
   ls.d_exp = d_exp;

@@ -112,6 +112,19 @@ inline int mask_chunks(const Layout& L) {
   return (int)((L.max_view_pix + kMaskChunk - 1) / kMaskChunk);
 }
 
+// The fused step's chunks of per-tile loss partials: view v has tile_chunks(its
+// tiles) of them, whose sums lie in the place of its blocks of the plain loss
+// (one per 256 pixels, from first_blk[v] on, 3 floats each).  Every tile holds a
+// pixel of its view, so ceil(tiles / 2048) <= ceil(pixels / 256): they fit
+// whatever the sizes of the views.
+constexpr int kTileChunk = 2048;
+__host__ __device__ inline int64_t tile_chunks(int64_t tiles) {
+  return (tiles + kTileChunk - 1) / kTileChunk;
+}
+__host__ __device__ inline int64_t loss_chunk_at(const int64_t* first_blk, int v, int64_t c) {
+  return 3 * (first_blk[v] + c);
+}
+
 // misc counters (uint32 slots at o_misc)
 // misc words: pair count, overflow flag, visible-slot count, long-slot count,
 // pairs actually emitted (min of the pair count, the capacity and the pairs of
