@@ -441,13 +441,13 @@ ROGS_API int rogs_meshgrid_layout(rogs_ctx* ctx, const rogs_pose* poses, int32_t
  * northern edge.  Every chunk of chunk_px x chunk_px pixels (smaller at the
  * right and bottom edges) is one orthographic camera looking straight down
  * from `height` (rogs_bev_camera), rendered with rogs_project + rogs_bin_sort
- * (pair counts read back for a few chunks at a time) + rogs_render_fwd
- * straight into `out`:
+ * (host count, one sync per chunk) + rogs_render_fwd straight into `out`:
  * the planes selected by `channels` (ROGS_CH_* as for serving, in the order
  * RGB, SEM, D, A, ELEV, each W x H floats; ELEV = height - D / A, NaN where
  * A = 0).  ws: device workspace of rogs_bev_workspace_size bytes for the
- * given pair capacity; a chunk with more pairs stops the export with
- * ROGS_ECAPACITY and *n_pairs_max (nullable) = the largest pair count seen. */
+ * given pair capacity; a chunk with more pairs stops the export before it is
+ * written, with ROGS_ECAPACITY and *n_pairs_max (nullable) = the largest pair
+ * count seen. */
 ROGS_API void rogs_bev_camera(double x0, double y0, int32_t W, int32_t H, float m_per_px,
                               int32_t ox, int32_t oy, int32_t cw, int32_t ch, float height,
                               rogs_camera* cam);

@@ -468,39 +468,9 @@ int render_batch(rogs_ctx* c, const rogs_surfels* s, void* ws, float* out_images
   return check_launch(c, "rogs_render_fwd");
 }
 
-int fail_capacity(rogs_ctx* c, int64_t n_pairs, int64_t n_slots) {
-  return fail(c, ROGS_ECAPACITY, "capacity (" + std::to_string(c->L.cap) + " pairs, " +
-                                     std::to_string(c->L.scap) + " slots) too small for " +
-                                     std::to_string(n_pairs) + " pairs, " +
-                                     std::to_string(n_slots) + " slots");
-}
-
 }  // namespace
 
 namespace rogs {
-
-int ctx_request_counts(rogs_ctx* c, void* ws, int k, void* stream) {
-  int r = need_batch(c, ws, false);
-  if (r != ROGS_OK) return r;
-  hipError_t e = hipMemcpyAsync(c->readback + 4 * k, at<void>(ws, c->L.o_misc), 16,
-                                hipMemcpyDeviceToHost, static_cast<hipStream_t>(stream));
-  return e == hipSuccess ? ROGS_OK : hip_fail(c, e, "rogs_pair_count");
-}
-
-int ctx_check_counts(rogs_ctx* c, int n, int64_t* worst, void* stream) {
-  hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail(c, e, "rogs_pair_count");
-  for (int k = 0; k < n; ++k) {
-    const int64_t pairs = c->readback[4 * k + kMiscPairs];
-    c->last_visible = c->readback[4 * k + kMiscVisible];
-    *worst = std::max(*worst, pairs);
-    if (pairs > c->L.cap || c->last_visible > c->L.scap) {
-      c->sorted = false;
-      return fail_capacity(c, pairs, c->last_visible);
-    }
-  }
-  return ROGS_OK;
-}
 
 int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
                     const rogs_render_opts* opts, void* ws, size_t ws_bytes,
@@ -657,7 +627,11 @@ int rogs_bin_sort(rogs_ctx* c, void* ws, int64_t* n_pairs_out, uint32_t flags, v
     if (r != ROGS_OK) return r;
     n_vis = c->last_visible;
     if (n_pairs_out) *n_pairs_out = n_host;
-    if (n_host > c->L.cap || n_vis > c->L.scap) return fail_capacity(c, n_host, n_vis);
+    if (n_host > c->L.cap || n_vis > c->L.scap)
+      return fail(c, ROGS_ECAPACITY, "capacity (" + std::to_string(c->L.cap) + " pairs, " +
+                                         std::to_string(c->L.scap) + " slots) too small for " +
+                                         std::to_string(n_host) + " pairs, " +
+                                         std::to_string(n_vis) + " slots");
   } else if (n_pairs_out) {
     *n_pairs_out = -1;
   }

@@ -60,7 +60,6 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
   if (r != ROGS_OK) return rogs::ctx_fail(c, r, "rogs_bev_export: invalid surfels or options");
   if (ws_bytes < need) return rogs::ctx_fail(c, ROGS_ENOMEM, "rogs_bev_export: workspace too small");
   int64_t worst = 0;
-  int pending = 0;                 // chunks whose counts have not been read
   for (int oy = 0; oy < H; oy += chunk_px) {
     for (int ox = 0; ox < W; ox += chunk_px) {
       const int cw = std::min(chunk_px, W - ox), ch = std::min(chunk_px, H - oy);
@@ -71,20 +70,14 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
       if (r != ROGS_OK) return rogs::ctx_fail(c, r, "rogs_bev_export: chunk layout");
       const rogs::ViewOut vo{(uint32_t)ROGS_CH_ALL, out + (int64_t)oy * W + ox, height};
       r = rogs::ctx_project_own(c, s, &cam, 1, opts, ws, wsb, pair_capacity, stream, &vo);
-      if (r == ROGS_OK) r = rogs_bin_sort(c, ws, nullptr, 0u, stream);
-      if (r == ROGS_OK) r = rogs::ctx_request_counts(c, ws, pending, stream);
+      int64_t n = 0;
+      if (r == ROGS_OK) r = rogs_bin_sort(c, ws, &n, ROGS_SYNC_COUNT, stream);
+      worst = std::max(worst, n);
+      if (n_pairs_max) *n_pairs_max = worst;
       if (r != ROGS_OK) return r;
       // only the planes the export asks for are composited
       r = rogs::ctx_render_own(c, s, ws, {channels, true, (int64_t)W * H, W}, stream);
       if (r != ROGS_OK) return r;
-      // the device waits for the host once per kCountReads chunks (with a wait
-      // in every chunk an export of four took 747 us, 733 us this way)
-      const bool last = H - oy <= chunk_px && W - ox <= chunk_px;
-      if (++pending < rogs::kCountReads && !last) continue;
-      r = rogs::ctx_check_counts(c, pending, &worst, stream);
-      if (n_pairs_max) *n_pairs_max = worst;
-      if (r != ROGS_OK) return r;
-      pending = 0;
     }
   }
   return ROGS_OK;

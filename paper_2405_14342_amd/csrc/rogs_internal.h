@@ -785,13 +785,6 @@ void ctx_fused_forget(rogs_ctx* c);
 int ctx_project_own(rogs_ctx* c, const rogs_surfels* s, const rogs_camera* cams, int32_t n_views,
                     const rogs_render_opts* opts, void* ws, size_t ws_bytes,
                     int64_t pair_capacity, void* stream, const ViewOut* outs);
-// Counts of several batches without a wait for each: ctx_request_counts queues
-// the read-back of this batch's as number k (< kCountReads), ctx_check_counts
-// waits, takes the largest pair count of the first n into worst up to the first
-// that overflowed, and fails as rogs_bin_sort does if one did.
-constexpr int kCountReads = 4;
-int ctx_request_counts(rogs_ctx* c, void* ws, int k, void* stream);
-int ctx_check_counts(rogs_ctx* c, int n, int64_t* worst, void* stream);
 int ctx_render_own(rogs_ctx* c, const rogs_surfels* s, void* ws, const FwdArgs& fa, void* stream);
 void launch_loss(const Layout& L, void* ws, const float* out, const rogs_targets* t, float* G,
                  float* loss_out, float* d_exp, hipStream_t st);
