@@ -75,8 +75,9 @@ int rogs_bev_export(rogs_ctx* c, const rogs_surfels* s, const rogs_render_opts* 
       worst = std::max(worst, n);
       if (n_pairs_max) *n_pairs_max = worst;
       if (r != ROGS_OK) return r;
-      // only the planes the export asks for are composited
-      r = rogs::ctx_render_own(c, s, ws, {channels, true, (int64_t)W * H, W}, stream);
+      // only the planes the export asks for are composited; there is no backward
+      // of an export, so no per-pixel state is kept for one
+      r = rogs::ctx_render_own(c, s, ws, {channels, false, (int64_t)W * H, W}, stream);
       if (r != ROGS_OK) return r;
     }
   }

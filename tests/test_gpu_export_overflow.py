@@ -67,3 +67,21 @@ def test_an_overflowing_chunk_is_not_written(at):
             assert torch.equal(a.nan_to_num(-1.0), b.nan_to_num(-1.0)), k
         else:
             assert (a == -7.0).all(), k
+
+
+def test_no_backward_after_an_export():
+    """rogs_render_bwd needs a rogs_render_fwd of every plane: the images of an
+    export lie in the stitched image, not in the batch's layout."""
+    st = _state()
+    L, surf, size, worst = B.load_library(), st.surfels(), ctypes.c_size_t(0), ctypes.c_int64(0)
+    cap = 1 << 18
+    assert L.rogs_bev_workspace_size(ctypes.byref(surf), 64, ctypes.byref(st.opts), cap,
+                                     ctypes.byref(size)) == B.OK
+    ws = torch.empty(size.value, dtype=torch.uint8, device="cuda")
+    out = torch.empty((B.channel_planes(B.CH_ALL, 2), 64, 64), device="cuda")
+    assert L.rogs_bev_export(st.rg.h, ctypes.byref(surf), ctypes.byref(st.opts), 0.0, 0.0, 64, 64, M,
+                             64, HEIGHT, B.CH_ALL, B.ptr(out), B.ptr(ws), size.value, cap,
+                             ctypes.byref(worst), B._stream(None)) == B.OK
+    G = torch.zeros_like(out)
+    with pytest.raises(B.RogsError, match="ESTATE"):
+        st.rg.render_bwd(surf, ws, out, G, st.grads)
