@@ -1324,36 +1324,42 @@ __global__ __launch_bounds__(64) void k_count_work(
 
 template <int C, int NW>
 void fwd_launch(const Layout& L, void* ws, float* out, const FwdArgs& fa, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_fwd<C, NW>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0, st,
-                     at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
-                     L.t_eps, at<const uint4>(ws, L.o_tinfo),
-                     at<const uint32_t>(ws, L.o_spair),
-                     at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out,
-                     fa.save ? at<float>(ws, L.o_tfin) : nullptr, at<uint32_t>(ws, L.o_nlast),
-                     at<float2>(ws, L.o_drel), fa.mask,
-                     reinterpret_cast<const ViewOutDev*>(at<int64_t>(ws, L.o_lpart) + L.V + 1), fa.plane,
-                     fa.row);
+  launch_bands(L.total_tiles, 64 * NW, [&](int64_t first, unsigned n) {
+    hipLaunchKernelGGL((k_render_fwd<C, NW>), dim3(n), dim3(64 * NW), 0, st,
+                       at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
+                       L.t_eps, at<const uint4>(ws, L.o_tinfo) + first,
+                       at<const uint32_t>(ws, L.o_spair),
+                       at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out,
+                       fa.save ? at<float>(ws, L.o_tfin) : nullptr, at<uint32_t>(ws, L.o_nlast),
+                       at<float2>(ws, L.o_drel), fa.mask,
+                       reinterpret_cast<const ViewOutDev*>(at<int64_t>(ws, L.o_lpart) + L.V + 1),
+                       fa.plane, fa.row);
+  });
 }
 
 template <int C, int NW, int KS>
 void bwd_launch(const Layout& L, void* ws, const float* out, const float* G, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_bwd<C, NW, KS>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0,
-                     st, at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
-                     at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_vals),
-                     at<const uint32_t>(ws, L.o_spair),
-                     at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out, G,
-                     at<const float>(ws, L.o_tfin), at<const uint32_t>(ws, L.o_nlast),
-                     at<const float2>(ws, L.o_drel), at<float>(ws, L.o_gpair));
+  launch_bands(L.total_tiles, 64 * NW, [&](int64_t first, unsigned n) {
+    hipLaunchKernelGGL((k_render_bwd<C, NW, KS>), dim3(n), dim3(64 * NW), 0, st,
+                       at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
+                       at<const uint4>(ws, L.o_tinfo) + first, at<const uint32_t>(ws, L.o_vals),
+                       at<const uint32_t>(ws, L.o_spair),
+                       at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat), out, G,
+                       at<const float>(ws, L.o_tfin), at<const uint32_t>(ws, L.o_nlast),
+                       at<const float2>(ws, L.o_drel), at<float>(ws, L.o_gpair));
+  });
 }
 
 template <int C, int NW, int KS>
 void step_launch(const Layout& L, void* ws, const FusedLoss& fl, hipStream_t st) {
-  hipLaunchKernelGGL((k_render_step<C, NW, KS>), dim3((unsigned)L.total_tiles), dim3(64 * NW), 0,
-                     st, at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
-                     L.t_eps, at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_vals),
-                     at<const uint32_t>(ws, L.o_spair),
-                     at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat),
-                     at<float>(ws, L.o_gpair), fl);
+  launch_bands(L.total_tiles, 64 * NW, [&](int64_t first, unsigned n) {
+    hipLaunchKernelGGL((k_render_step<C, NW, KS>), dim3(n), dim3(64 * NW), 0, st,
+                       at<const ViewDev>(ws, L.o_views), L.V, L.N, L.q_cut, L.alpha_max,
+                       L.t_eps, at<const uint4>(ws, L.o_tinfo) + first,
+                       at<const uint32_t>(ws, L.o_vals), at<const uint32_t>(ws, L.o_spair),
+                       at<const float4>(ws, L.o_rec), at<const float4>(ws, L.o_feat),
+                       at<float>(ws, L.o_gpair), fl);
+  });
 }
 
 // which: 0 forward, 1 backward, 2 fused step

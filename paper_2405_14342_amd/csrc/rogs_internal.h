@@ -740,6 +740,19 @@ struct AdamArgs {
 
 // ------------------------------------------------------------------ launchers
 
+// Calls launch(first, count) for consecutive parts of `blocks` blocks of
+// `threads` threads.  A grid dimension holds fewer than 2^32 threads: the
+// runtime forms the product in 32 bits and takes a larger grid, without an error,
+// as what remains of it past 2^32 (refused only if that is 0).
+template <typename Launch>
+inline void launch_bands(int64_t blocks, int threads, Launch launch) {
+  const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+  for (int64_t b = 0; b < blocks; b += most) {
+    const int64_t n = blocks - b < most ? blocks - b : most;
+    launch(b, (unsigned)n);
+  }
+}
+
 // Copies the view table (bytes of pinned host memory) into the workspace and
 // clears the batch's counters.
 void launch_upload(const Layout& L, void* ws, const void* stage, size_t bytes, hipStream_t st);

@@ -1,8 +1,8 @@
 // Host-only checks of the workspace layout (test infrastructure, built by the
 // package's build step and run without a GPU).  For batches of mixed view
 // sizes in every tile shape, the places that kernels derive from a view's
-// index lie inside the region that the layout reserves for them.  Prints
-// "layout checks: ok".
+// index lie inside the region that the layout reserves for them.  Also the parts
+// of a launch that one grid cannot hold.  Prints "layout checks: ok".
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -65,7 +65,21 @@ static void loss_chunks(const Sizes& sizes, int tw, int th) {
   }
 }
 
+// A launch in parts: every block once, in order, and no part of 2^32 threads.
+static void bands(int64_t blocks, int threads) {
+  int64_t next = 0;
+  rogs::launch_bands(blocks, threads, [&](int64_t first, unsigned n) {
+    CHECK(first == next && n > 0 && (uint64_t)n * threads < (1ull << 32));
+    next = first + n;
+  });
+  CHECK(next == blocks);
+}
+
 int main() {
+  for (int threads : {64, 128, 256})
+    for (int64_t blocks : {int64_t(0), int64_t(1), (int64_t(1) << 24) - 1, int64_t(1) << 24,
+                           (int64_t(1) << 24) + 5, int64_t(1) << 26, (int64_t(1) << 31) - 1})
+      bands(blocks, threads);
   const int shapes[][2] = {{16, 4}, {8, 8}, {64, 1}, {1, 64}, {16, 8}, {64, 2}, {1, 128}, {16, 16}, {64, 4}, {1, 256}};
   std::mt19937 rng(5);
   for (const auto& t : shapes) {
