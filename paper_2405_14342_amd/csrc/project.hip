@@ -175,24 +175,26 @@ __device__ __forceinline__ void project_block(
 // index v * nb + range, to list, and writes the zero counts of the others.
 // Most pairs of a long road go here (82 % of 24 views of a 200 m strip, more of
 // a longer one), and a block of the projection's own launch for each of them is
-// bound by the rate at which blocks start (kProjListMin).  Extra blocks as in project_side_block from block
-// range_blocks on.
+// bound by the rate at which blocks start (kProjListMin).  Extra blocks as in
+// project_side_block from block range_blocks on; this launch's blocks start at
+// first_block.
 __global__ __launch_bounds__(kProjBlock) void k_project_list(
-    const ViewDev* __restrict__ views, int V, int N, int nb, int range_blocks, double r_cut,
-    double sqrt_eps, const float* __restrict__ px, const float* __restrict__ py,
+    const ViewDev* __restrict__ views, int V, int N, int nb, int first_block, int range_blocks,
+    double r_cut, double sqrt_eps, const float* __restrict__ px, const float* __restrict__ py,
     const float* __restrict__ pz, const float* __restrict__ ps, uint32_t* __restrict__ part,
     uint32_t* __restrict__ partv, uint32_t* __restrict__ list, uint32_t* __restrict__ misc,
     const uint8_t* __restrict__ mask, int nmb, uint32_t* __restrict__ mpart,
     uint32_t* __restrict__ zero_words, int64_t n_zero) {
   __shared__ uint32_t s_w[kProjBlock / 64];
-  if (blockIdx.x >= (unsigned)range_blocks) {
-    const int k = (int)blockIdx.x - range_blocks;
+  const int block = first_block + (int)blockIdx.x;
+  if (block >= range_blocks) {
+    const int k = block - range_blocks;
     project_side_block(views, V, k % nmb, k / nmb, mask, nmb, mpart, zero_words, n_zero, s_w);
     return;
   }
   constexpr int kPer = kProjBlock / 64;
   const int lane = threadIdx.x & 63;
-  const int range = (int)blockIdx.x * kPer + (int)(threadIdx.x >> 6);
+  const int range = block * kPer + (int)(threadIdx.x >> 6);
   if (range >= nb) return;
   const int i0 = range * kProjBlock + lane;
   float x[kPer], y[kPer];
@@ -609,9 +611,11 @@ void launch_project(const Layout& L, void* ws, const rogs_surfels* s, hipStream_
   uint32_t* list = listed ? at<uint32_t>(ws, L.o_pos) : nullptr;   // written by the compaction later
   const int range_blocks = (L.nb + kProjBlock / 64 - 1) / (kProjBlock / 64);
   if (listed)
-    hipLaunchKernelGGL(k_project_list, dim3((unsigned)(range_blocks + nmb * L.V)),
-                       dim3(kProjBlock), 0, st, views, L.V, L.N, L.nb, range_blocks, r_cut, sqrt_eps, s->x, s->y, s->z, s->s, part, partv,
-                       list, misc, mask, nmb, mpart, tcnt, n_zero);
+    launch_bands(range_blocks + (int64_t)nmb * L.V, kProjBlock, [&](int64_t first, unsigned n) {
+      hipLaunchKernelGGL(k_project_list, dim3(n), dim3(kProjBlock), 0, st, views, L.V, L.N, L.nb,
+                         (int)first, range_blocks, r_cut, sqrt_eps, s->x, s->y, s->z, s->s, part,
+                         partv, list, misc, mask, nmb, mpart, tcnt, n_zero);
+    });
   const dim3 grid = listed ? dim3((unsigned)std::min<int64_t>((int64_t)L.V * L.nb, kProjListBlocks))
                            : dim3(L.nb + nmb, L.V);
   hipLaunchKernelGGL(k_project, grid, dim3(kProjBlock), 0, st, views, L.V, L.N, L.nb, L.eps2d,

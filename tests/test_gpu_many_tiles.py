@@ -69,3 +69,42 @@ def test_fused_step():
     # both, and the views are added in the same order
     loss = a.loss.item()
     assert loss > 0 and abs(b.fused_status()["loss"] - loss) <= 200 * 2.0 ** -24 * loss
+
+
+def test_mask_counts_of_mixed_views():
+    """One view of 16384 x 8193 and 1029 of 8 x 8: the fused step's mask chunks,
+    counted per view by the largest view's number, are more blocks than one grid
+    holds.  Each view's loss is divided by its own mask count: the fused step is
+    the batched step."""
+    rng = np.random.default_rng(12)
+    n = 8300                                   # 33 ranges x 1030 views: pairs are listed
+    cams = [synth.ortho_bev_camera((20.0, 20.0), 10.0, 16384, 8193, m_per_px=0.0025)]
+    cams += [synth.ortho_bev_camera(rng.uniform(0, 40, 2), 10.0, 8, 8, m_per_px=0.05)
+             for _ in range(1029)]
+    q = np.concatenate([np.ones((1, n)), np.zeros((3, n))])
+    sc = synth.custom_scene(*rng.uniform(0, 40, (2, n)), rng.normal(0, 0.1, n), q,
+                            np.full((2, n), 0.02), rng.uniform(0.2, 0.7, n), rng.uniform(0, 1, (3, n)),
+                            rng.normal(0, 1, (1, n)), cams, targets=[])
+
+    def state():
+        st = TrainState(sc, opts=B.make_opts(tile_w=16, tile_h=16))
+        npix = sum(st.npix)
+        gen = torch.Generator("cuda").manual_seed(4)
+        st.tgt_rgb = torch.rand(3 * npix, generator=gen, device="cuda")
+        st.tgt_label = torch.zeros(npix, dtype=torch.uint8, device="cuda")
+        st.tgt_mask = (torch.rand(npix, generator=gen, device="cuda") < 0.7).to(torch.uint8)
+        return st
+
+    a = state()
+    a.step_batched(total_steps=5)
+    torch.cuda.synchronize()
+    ref = {k: getattr(a, k).clone() for k in ("grads", "params", "m", "v")}
+    loss = a.loss.item()
+    del a
+    torch.cuda.empty_cache()
+    b = state()
+    b.step_fused(total_steps=5, grads_out=True)
+    torch.cuda.synchronize()
+    for k, t in ref.items():
+        assert torch.equal(t, getattr(b, k)), k
+    assert loss > 0 and abs(b.fused_status()["loss"] - loss) <= 200 * 2.0 ** -24 * loss
