@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kNNBlock) void k_nn_search(int n, const float* __re
 // the exclusive running count of road cells before each word (row-major), so a
 // cell's surfel is a word's count plus a bit count: at 1 km of road (11M
 // cells) 1.4 + 0.7 MB instead of two 44 MB arrays.
-__host__ __device__ inline int row_words(int W) { return (W + 63) / 64; }
+__host__ __device__ inline int row_words(int W) { return W / 64 + (W % 64 != 0); }
 
 __device__ __forceinline__ bool road_cell(const unsigned long long* __restrict__ bits, int wr,
                                           int row, int col) {
@@ -528,7 +528,7 @@ constexpr int kMaxRadius = 4096;     // the entry point's limit
 
 __global__ __launch_bounds__(256) void k_road_mask(int np, const rogs_pose* __restrict__ poses,
                                                    double x0, double y0, float h, int r, int W,
-                                                   int H, int row0,
+                                                   int H, int word0, int row0,
                                                    unsigned long long* __restrict__ bits,
                                                    uint32_t* __restrict__ cnt) {
 #pragma clang fp contract(off)
@@ -544,7 +544,8 @@ __global__ __launch_bounds__(256) void k_road_mask(int np, const rogs_pose* __re
     while ((w + 1) * (w + 1) <= rem) ++w;
     s_half[dy] = w;
   }
-  const int c0 = blockIdx.x * 64, r0 = row0 + (int)blockIdx.y * 256, row = r0 + tid;
+  const int word = word0 + (int)blockIdx.x;
+  const int c0 = word * 64, r0 = row0 + (int)blockIdx.y * 256, row = r0 + tid;
   const int c1 = min(c0 + 63, W - 1), r1 = min(r0 + 255, H - 1);
   unsigned long long m = 0ull;
   for (int k0 = 0; k0 < np; k0 += 256) {
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(256) void k_road_mask(int np, const rogs_pose* __re
     }
   }
   if (row < H) {
-    const int64_t q = (int64_t)row * row_words(W) + blockIdx.x;
+    const int64_t q = (int64_t)row * row_words(W) + word;
     bits[q] = m;
     cnt[q] = (uint32_t)__popcll(m);
   }
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(256) void k_layout_fill(int W, int H,
                                                      const uint32_t* __restrict__ before,
                                                      double x0, double y0, float h, int np,
                                                      const rogs_pose* __restrict__ poses, int64_t n,
-                                                     int row0, int32_t* __restrict__ idx,
+                                                     int col0, int row0, int32_t* __restrict__ idx,
                                                      float* __restrict__ x, float* __restrict__ y,
                                                      float* __restrict__ z, float* __restrict__ q,
                                                      int32_t* __restrict__ nbr) {
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(256) void k_layout_fill(int W, int H,
   __shared__ float4 s_q[kFillCand];                  // the candidates' rotations
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wr = row_words(W);
-  const int c0 = blockIdx.x * kFill, r0 = row0 + (int)blockIdx.y * kFill;
+  const int c0 = (col0 + (int)blockIdx.x) * kFill, r0 = row0 + (int)blockIdx.y * kFill;
   const int col = c0 + tid % kFill, rowt = r0 + tid / kFill;
   uint32_t road = 0u;
 #pragma unroll
@@ -858,12 +859,16 @@ size_t layout_scratch_bytes(int W, int H, int np) {
   return layout_scratch(W, H).total;
 }
 
-// Blocks of `side` rows in bands of at most 65535 (the grid's y extent).
+// gx columns of blocks of `side` rows, as parts of at most 65535 rows of blocks
+// (the grid's y extent) and fewer than 2^32 threads to a row: launch(grid, first
+// column of blocks, first row).
 template <typename Launch>
-static void row_bands(int H, int side, Launch launch) {
+static void bands(int64_t gx, int H, int side, Launch launch) {
   const int64_t gy = ((int64_t)H + side - 1) / side;
   for (int64_t b = 0; b < gy; b += 65535)
-    launch((unsigned)std::min<int64_t>(gy - b, 65535), (int)(b * side));
+    launch_bands(gx, 256, [&](int64_t first, unsigned n) {
+      launch(dim3(n, (unsigned)std::min<int64_t>(gy - b, 65535)), (int)first, (int)(b * side));
+    });
 }
 
 void launch_layout_mask(const rogs_pose* poses, int np, double x0, double y0, float h, int W,
@@ -871,10 +876,9 @@ void launch_layout_mask(const rogs_pose* poses, int np, double x0, double y0, fl
   const LayoutScratch s = layout_scratch(W, H);
   uint8_t* base = static_cast<uint8_t*>(scratch);
   uint32_t* before = reinterpret_cast<uint32_t*>(base + s.o_before);
-  row_bands(H, 256, [&](unsigned gy, int row0) {
-    hipLaunchKernelGGL(k_road_mask, dim3((unsigned)row_words(W), gy), dim3(256), 0, st, np, poses,
-                       x0, y0, h, r, W, H, row0,
-                       reinterpret_cast<unsigned long long*>(base + s.o_bits), before);
+  bands(row_words(W), H, 256, [&](dim3 grid, int word0, int row0) {
+    hipLaunchKernelGGL(k_road_mask, grid, dim3(256), 0, st, np, poses, x0, y0, h, r, W, H, word0,
+                       row0, reinterpret_cast<unsigned long long*>(base + s.o_bits), before);
   });
   scan_u32(before, before, s.words, n_dev, reinterpret_cast<uint32_t*>(base + s.o_tmp), st);
 }
@@ -884,11 +888,11 @@ void launch_layout_fill(const rogs_pose* poses, int np, double x0, double y0, fl
                         float* z, float* q, int32_t* nbr, hipStream_t st) {
   const LayoutScratch s = layout_scratch(W, H);
   const uint8_t* base = static_cast<const uint8_t*>(scratch);
-  row_bands(H, kFill, [&](unsigned gy, int row0) {
-    hipLaunchKernelGGL(k_layout_fill, dim3((unsigned)((W + kFill - 1) / kFill), gy), dim3(256), 0,
-                       st, W, H, reinterpret_cast<const unsigned long long*>(base + s.o_bits),
+  bands(((int64_t)W + kFill - 1) / kFill, H, kFill, [&](dim3 grid, int col0, int row0) {
+    hipLaunchKernelGGL(k_layout_fill, grid, dim3(256), 0, st, W, H,
+                       reinterpret_cast<const unsigned long long*>(base + s.o_bits),
                        reinterpret_cast<const uint32_t*>(base + s.o_before), x0, y0, h, np, poses,
-                       n, row0, idx, x, y, z, q, nbr);
+                       n, col0, row0, idx, x, y, z, q, nbr);
   });
 }
 
