@@ -43,7 +43,8 @@ def algorithmic_bytes(kernel: str, st, stats, C: int, fused: bool) -> float:
     FS = ((4 + C) + 3) // 4 * 4
     K = 11 + C
     if kernel == "project":
-        return N * (40 + 4 * FS) + slots * 4 + S * 40
+        # (fused: the loss masks are counted in the same launch)
+        return N * (40 + 4 * FS) + slots * 4 + S * 40 + (X if fused else 0)
     if kernel == "sort":
         # compaction (slot, count, position of each visible slot) + emission
         # offsets + one tile key, rank, slot and depth key per pair + the
@@ -65,15 +66,14 @@ def algorithmic_bytes(kernel: str, st, stats, C: int, fused: bool) -> float:
     if kernel == "render_fwd":
         return X * ((5 + C) * 4 + 8) + P * 8 + S * (32 + 4 * FS)
     if kernel == "loss":
-        if fused:   # mask count + per-view sums of the per-tile partials
-            return X * 1 + stats["tiles"] * 12
         return X * ((3 + C) * 4 + 14 + 1 + (5 + C) * 4)
     if kernel == "render_bwd":
         return X * ((5 + C) * 4 + (4 + C) * 4 + 8) + P * (8 + 4 * (10 + C)) + S * (32 + 4 * FS)
     if kernel == "proj_bwd":
         base = slots * 4 + S * 4 + P * 4 * (10 + C) + N * (40 + 4 * K)
-        if fused:   # + Adam: p, m, v read and written, s and alpha refreshed
-            return base - N * 4 * K + N * (K * 4 * 6 + 2 * 3 * 4)
+        if fused:   # + Adam: p, m, v read and written, s and alpha refreshed,
+            # and the per-view sums of the per-tile loss partials
+            return base - N * 4 * K + N * (K * 4 * 6 + 2 * 3 * 4) + stats["tiles"] * 12
         return base
     if kernel == "adam":
         return N * (K * 4 * 7 + 2 * 3 * 4) + V * 2 * 4 * 7

@@ -395,9 +395,9 @@ ROGS_API int rogs_elev_loss_static(rogs_ctx* ctx, int32_t n, const float* z, con
  * the xy-plane (squared distance in binary64 of the binary32 inputs, ties to
  * the lower point index: the brute-force result), idx[i] its index
  * (nullable).  The points are bucketed into a uniform grid of about 2m cells
- * over the bounding box of surfels and points, and each surfel searches
- * cells with points, row by row outward, until none left can hold a nearer point:
- * O(n + m) work for points spread like road returns.  Device arrays; 1 <= m <=
+ * over the bounding box of surfels and points, and each surfel searches blocks
+ * of 8 x 8 cells, by row outward from its own, until none left can hold a nearer
+ * point: O(n + m) work for points spread like road returns.  Device arrays; 1 <= m <=
  * 2^29.  scratch: caller-owned device memory, 256-byte aligned, of
  * rogs_lidar_scratch_bytes(n, m) bytes (the grid, the points in cell order). */
 ROGS_API size_t rogs_lidar_scratch_bytes(int32_t n, int32_t m);
@@ -462,7 +462,7 @@ ROGS_API int rogs_bev_export(rogs_ctx* ctx, const rogs_surfels* s, const rogs_re
 
 /* ------------------------------------------------------ autotuner
  * Chooses the launch configuration for a workload: the tile shape (which
- * also sets the pixels per lane, tile_w * tile_h / 64), the LDS staging depth
+ * also sets the waves per tile, tile_w * tile_h / 64), the LDS staging depth
  * (opts->stage) and a tile shape per resolution class.  Every configuration
  * renders the same values, since the per-pixel rule does not depend on it
  * (Sec. 3.3.1 with the 3-sigma cut); they differ in the number of (surfel,
@@ -542,7 +542,9 @@ typedef struct {
 
 /* map: device surfel arrays that stay valid and unchanged while the server
  * lives.  arena: caller-owned device memory (256-byte aligned) holding the
- * batch workspaces and images; the server allocates no device memory.
+ * batch workspaces and, for sizing, the room of one image per view (views are
+ * rendered straight into their own output); the server allocates no device
+ * memory.
  * lanes (1..8): worker threads, each with its own stream and an equal share
  * of the arena; an idle lane takes the queued requests, so batches on
  * different lanes overlap on the device.  device: HIP device ordinal.
@@ -578,8 +580,10 @@ ROGS_API int rogs_batch_stats(rogs_ctx* ctx, void* ws, int64_t* stats, void* str
  * (arrays of ROGS_PROF_GROUPS entries; n must be >= ROGS_PROF_GROUPS) since
  * the previous read, and resets them.  Group names: rogs_prof_name.  In
  * the fused step, group "fused_graph" times the whole graph launch (the
- * kernels inside a graph carry no events; ROGS_FUSED_EAGER times them), and
- * "render_step" its combined forward + loss + backward compositing. */
+ * kernels inside a graph carry no events; ROGS_FUSED_EAGER times them),
+ * "render_step" its combined forward + loss + backward compositing, and
+ * "proj_bwd" the slot sums with the loss sums beside them, the grid-side terms,
+ * the adjoint and Adam; "loss" and "adam" stay empty. */
 #define ROGS_PROF_GROUPS 12
 ROGS_API int rogs_prof_enable(rogs_ctx* ctx, int32_t on);
 ROGS_API int rogs_prof_read(rogs_ctx* ctx, double* ms, int64_t* launches, int32_t n);

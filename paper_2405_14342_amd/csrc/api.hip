@@ -201,7 +201,7 @@ int make_layout(const rogs_surfels* s, const rogs_camera* cams, int n_views,
   l.o_partv = take(4 * (size_t)l.V * l.nb);
   l.o_parttmp = take(4 * 2 * scan_tmp_words((int64_t)l.V * l.nb));   // one sums table each
   l.o_keys = take(4 * (size_t)cap);          // tile of each pair
-  l.o_keys2 = take(4 * (size_t)cap);         // alternate keys of the pair sort
+  l.o_keys2 = take(4 * (size_t)cap);         // depth keys of the sorted runs, for their merge
   l.o_vals = take(4 * (size_t)cap);
   l.o_vals2 = take(4 * (size_t)cap);
   l.o_pslot = take(4 * (size_t)cap);
@@ -881,7 +881,6 @@ rogs::AdamArgs fused_adam_args(const rogs_optim* o, const Layout& L, void* ws, c
 }
 
 // The whole step on one stream; captured once into a graph or run eagerly.
-// Returns the sort's buffer parity.
 int fused_sequence(rogs_ctx* c, Layout& L, const rogs_train_state* t, const rogs_targets* tg,
                    const rogs_optim* o, void* ws, hipStream_t st) {
   rogs_surfels s = fused_surfels(t);

@@ -1,5 +1,5 @@
 // Launch-configuration autotuner (rogs_autotune).  The tile shape (and with
-// it the pixels per lane), the LDS staging depth and the per-view tile shapes
+// it the waves per tile), the LDS staging depth and the per-view tile shapes
 // are free parameters of the implementation: the per-pixel rule (q32 <= q_cut,
 // Sec. 3.3.1 with a 3-sigma cut) does not depend on them, so every choice
 // renders the same values; they change how many (surfel, tile) pairs are

@@ -667,7 +667,7 @@ void proj_bwd_launch(const Layout& L, void* ws, const rogs_surfels* s, float* gr
 
 // One thread per pixel; grid.y = view, so a block never straddles views.
 // Writes dL/dO (all 5 + C channels; D and A rows 0) and per-block partial
-// sums (loss, da, db) that k_loss_final adds in a fixed order.
+// sums (loss, da, db) that k_loss_views adds in a fixed order.
 template <int C>
 __global__ __launch_bounds__(kLossBlock) void k_loss_v(
     const ViewDev* __restrict__ views, int V, const int64_t* __restrict__ first_blk,

@@ -943,9 +943,9 @@ __device__ __forceinline__ void backward_block(const TileGeom& tg, float qcut, f
         part16[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(L.mask[w] >> j0)) &
                     0xffffu;
       // kB entries side by side: those of one part each, whose sums are that
-      // part's, or general ones, where a part that an entry does not reach
-      // adds +0 (its rows hold leftovers), which changes no bit of a sum that
-      // starts at +0.  Entries past n add nothing and store nothing.
+      // part's, or general ones, where the parts that an entry does not reach
+      // are left out (their rows hold leftovers): their share would be +0, which
+      // changes no bit of a sum that starts at +0.  Entries past n add nothing and store nothing.
       constexpr int kB = 4;
       for (int i0 = wv; i0 < n; i0 += kB * NW) {
         float pv[kB][NR], fs[kB], tot[kB];

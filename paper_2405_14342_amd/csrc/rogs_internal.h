@@ -820,9 +820,8 @@ void launch_proj_bwd_adam(const Layout& L, void* ws, const float* x, const float
                           float* m, float* v, float* s_act, float* a_act, float* grads_out,
                           const AdamArgs& aa, float* expo, const float* dexpo, float* me,
                           float* ve, const float* dzr, hipStream_t st);
-// Fused: per-view loss and dL/d(a, b) (overwritten) from the per-tile partials.
-// The fused step's slot sums, with its per-view loss sums, dL/d(a, b) and the
-// exposure's Adam step beside them.
+// The fused step's slot sums and, beside them, its per-view loss and dL/d(a, b)
+// (overwritten) from the per-tile partials and the exposure's Adam step.
 void launch_slot_loss_sums(const Layout& L, void* ws, float* d_exp, float* expo, float* m_exp,
                            float* v_exp, const AdamArgs& aa, hipStream_t st);
 void launch_mask_count(const Layout& L, void* ws, const uint8_t* mask, hipStream_t st);

@@ -28,7 +28,8 @@ constexpr int64_t kClearPerThread = 8;    // tile counters that a thread of the 
 // scan of the counts), and the first slot of every emission block of
 // kEmitPairs pairs (each block start lies in exactly one slot; only the nblk
 // launched blocks).  Block 0 also sets the overflow flag from the totals of
-// the count scans (the fused step's scan launch leaves it to this one).  With
+// the count scans (only their three-launch form, k_scan2_down, has set it
+// already).  With
 // feat (the fused step) nb more blocks pack the feature records of the ranges
 // that some view sees, beside the compaction and without a launch of their own.
 // Without feat the blocks clear the T tile counters, and blocks past nb do only
@@ -463,9 +464,6 @@ __global__ __launch_bounds__(256) void k_place(const uint32_t* __restrict__ keys
   vals[tstart[keys[e]] + rank[e]] = (uint32_t)e;
 }
 
-// Compositing work item of each launch position b: (tile, list begin, list
-// end, view | the tile's row in its view << kViewBits) of the tile order[b],
-// so a compositing wave starts from one load and needs no division.
 // Depth order inside each tile.  A tile's list holds its pairs in the order
 // the counters ranked them; these kernels order it by (t_z bits, emission
 // index e), which is the binary32 depth with ties by surfel id (emission runs
@@ -552,8 +550,8 @@ __device__ __forceinline__ void wave_sort_list(uint32_t beg, uint32_t len,
 // each wave sorts 64 R entries in registers, then two rounds of merging in LDS
 // double the runs, every element finding its place in the partner run by a
 // binary search (an element of the even run goes before equal ones of the odd
-// run, which only padding has).  Leaves element idx[r] = sorted position and v
-// = (t_z bits, e) in registers, and the sorted run in s.
+// run, which only padding has).  Leaves the run's elements (t_z bits, e) in s,
+// in order.
 template <int R>
 __device__ __forceinline__ void block_sort_run(uint32_t beg, uint32_t cnt,
                                                const uint32_t* __restrict__ vals,
@@ -815,22 +813,24 @@ __global__ __launch_bounds__(256) void k_tile_merge(const uint4* __restrict__ ti
 }
 
 // Tile layout: list start and range of every tile, and the compositing launch
-// order with a work item per launch position.  The launch order takes the
-// longest lists first: bucket d = 15 - (bit length of the list length,
-// capped at 15) ascending, tile index order inside a bucket (a tile's results
-// do not depend on when it runs; the order keeps the few very long far-field
-// lists from starting last and setting the kernel's end).  Inside each bucket
-// the launch positions are permuted in blocks of 64 (an 8 x 8 transpose), so
-// that runs of 8 consecutive tiles of the order (one tile row, mostly the
-// same surfels) take launch positions 8 apart: the workgroups of one launch
-// go to the 8 XCDs in turn, so such a run is composited by one XCD and its
-// surfels' records stay in that XCD's L2.  Three launches: per block of
-// kTileBlk tiles the pair count and the bucket sizes (k_tile_part), their
-// exclusive scans down the blocks and the totals (k_tile_top), then the
-// placement (k_tile_layout).  Up to kTileSelf blocks each block of the
-// placement counts the tiles itself, a pass over at most 16 KB, instead of the
-// other two launches: 1 block 16 -> 9 us, 3 blocks 14 -> 13 us; at 11 blocks
-// the passes take 20 us, twice the launches' time.
+// order with a work item per launch position: (tile, list begin, list end,
+// view | the tile's row in its view << kViewBits), so a compositing wave
+// starts from one load and needs no division. The launch order takes the
+// longest lists first: bucket d = 15 - (bit length of the list length, capped
+// at 15) ascending, tile index order inside a bucket (a tile's results do not
+// depend on when it runs; the order keeps the few very long far-field lists
+// from starting last and setting the kernel's end). Inside each bucket the
+// launch positions are permuted in blocks of 64 (an 8 x 8 transpose), so that
+// runs of 8 consecutive tiles of the order (one tile row, mostly the same
+// surfels) take launch positions 8 apart: the workgroups of one launch go to
+// the 8 XCDs in turn, so such a run is composited by one XCD and its surfels'
+// records stay in that XCD's L2. Three launches: per block of kTileBlk tiles
+// the pair count and the bucket sizes (k_tile_part), their exclusive scans
+// down the blocks and the totals (k_tile_top), then the placement
+// (k_tile_layout). Up to kTileSelf blocks each block of the placement counts
+// the tiles itself, a pass over at most 16 KB, instead of the other two
+// launches: 1 block 16 -> 9 us, 3 blocks 14 -> 13 us; at 11 blocks the passes
+// take 20 us, twice the launches' time.
 constexpr int64_t kTileSelf = 4;
 
 __device__ __forceinline__ uint32_t tile_bucket(uint32_t len) {
