@@ -1088,8 +1088,12 @@ void launch_ranges(const Layout& L, void* ws, hipStream_t st) {
                      at<uint32_t>(ws, L.o_vals), at<const uint32_t>(ws, L.o_pslot),
                      at<const uint32_t>(ws, L.o_pdep), at<uint32_t>(ws, L.o_spair),
                      at<uint32_t>(ws, L.o_keys2), at<uint32_t>(ws, L.o_vals2));
+  // a list of group bl has at least 2^(bl-1) entries and sort_runs = 2^(bl-10)
+  // items: no more than one item to 512 pairs
   if (merge)
-    hipLaunchKernelGGL(k_tile_merge, dim3(kMergeBlocks), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_tile_merge,
+                       dim3((unsigned)std::min<int64_t>(L.cap / (kSortRun / 2), kMergeBlocks)),
+                       dim3(256), 0, st,
                        at<const uint4>(ws, L.o_tinfo), at<const uint32_t>(ws, L.o_histtmp),
                        at<const uint32_t>(ws, L.o_pslot), at<const uint32_t>(ws, L.o_keys2),
                        at<const uint32_t>(ws, L.o_vals2), at<uint32_t>(ws, L.o_vals),
